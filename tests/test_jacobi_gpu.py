@@ -121,6 +121,20 @@ def test_jacobi_2d_marching_form(monkeypatch, shape, tsteps, tblock, cfg):
     assert_same(gpu_run(2, tsteps, A, B, tblock), oracle.jacobi_2d(tsteps, A, B), "jacobi_2d marching")
 
 
+@pytest.mark.parametrize("shape,tblock", [((400, 484), 16), ((401, 566), 8), ((257, 388), 16), ((193, 674), 10),
+                                          ((130, 416), 4)])
+def test_jacobi_2d_marching_tile_order(monkeypatch, shape, tblock):
+    """Several strips and segments, the workgroups that hold boundary cells
+    numbered first: the last column inside the halo of the last strip but one,
+    a last segment shorter than a pass.  Bit for bit against the oracle."""
+    monkeypatch.setenv("DCP_TUNING", "1")
+    monkeypatch.setenv("DCP_J2_MODE", "3")
+    A, B = inputs.jacobi_fields(2, shape[0], seed=11, n1=shape[1])
+    for tsteps in (33, 40):
+        say(f"jacobi_2d tile order shape={shape} tsteps={tsteps} tblock={tblock}")
+        assert_same(gpu_run(2, tsteps, A, B, tblock), oracle.jacobi_2d(tsteps, A, B), "jacobi_2d tile order")
+
+
 @pytest.mark.parametrize("tblock", [0, 1, 256])
 def test_jacobi_1d_paper_size_full_run(tblock):
     w = inputs.JACOBI_WORKLOADS["jacobi_1d_paper"]
