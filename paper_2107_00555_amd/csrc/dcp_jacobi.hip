@@ -50,58 +50,13 @@ struct J1Args {
 
 // vec16: every lane's two columns are one aligned 16-byte pair (n1 and hh
 // even, arrays 16-byte aligned), so loads and stores move both at once.
-// set: which tiles this launch covers: 0 = all, 1 = the interior rectangle
-// [r_lo, r_hi] x [c_lo, c_hi] of tiles whose region holds no boundary cell of
-// the array, 2 = the ring of the other tiles (see j2_tile).
 struct J2Args {
     const double *ain, *bin, *bfix;
     double *aout, *bout;
     int64_t n0, n1;
-    int inner_r, inner_c, tiles_r, tiles_c;
+    int inner_r, inner_c, tiles_r;
     int hh, nhalf, phase, write_b, vec16;
-    int set, r_lo, r_hi, c_lo, c_hi;
 };
-
-// Tile (row, column) of workgroup b (after the XCD renumbering).  Tiles run
-// column by column, so a tile's upper and lower neighbours (whose halos it
-// shares, the larger overlap) are recent in the same XCD's L2.
-__device__ __forceinline__ void j2_tile(const J2Args &a, int b, int &tr, int &tc) {
-    if (a.set == 0) {
-        tr = b % a.tiles_r;
-        tc = b / a.tiles_r;
-        return;
-    }
-    if (a.set == 1) {
-        const int nr = a.r_hi - a.r_lo + 1;
-        tr = a.r_lo + b % nr;
-        tc = a.c_lo + b / nr;
-        return;
-    }
-    // ring: the rows above and below the rectangle in full, then the columns
-    // left and right of it on the rectangle's rows
-    const int top = a.r_lo * a.tiles_c, below = (a.tiles_r - 1 - a.r_hi) * a.tiles_c;
-    if (b < top) {
-        tr = b / a.tiles_c;
-        tc = b % a.tiles_c;
-        return;
-    }
-    b -= top;
-    if (b < below) {
-        tr = a.r_hi + 1 + b / a.tiles_c;
-        tc = b % a.tiles_c;
-        return;
-    }
-    b -= below;
-    const int nr = a.r_hi - a.r_lo + 1, left = a.c_lo, right = a.tiles_c - 1 - a.c_hi;
-    if (b < nr * left) {
-        tr = a.r_lo + b / left;
-        tc = b % left;
-        return;
-    }
-    b -= nr * left;
-    tr = a.r_lo + b / right;
-    tc = a.c_hi + 1 + b % right;
-}
 
 __device__ __forceinline__ int j_xcd_remap(int b, int nb) {
     // consecutive workgroups go to different XCDs; number the tiles so that
@@ -248,163 +203,155 @@ __global__ void __launch_bounds__(64) j1_kernel(J1Args a) {
 }
 
 // ---------------------------------------------------------------- jacobi_2d
-// W waves per workgroup; wave w owns region rows [w*RPL, (w+1)*RPL) and lane
-// l the columns 2l and 2l+1, so the region is (W*RPL) x 128 cells.  West and
+// 16 waves per workgroup; wave w owns region rows [w*RPL, (w+1)*RPL) and lane
+// l the columns 2l and 2l+1, so the region is (16*RPL) x 128 cells.  West and
 // east neighbours across lanes come from DPP shifts, the rows above and below
 // a wave's band from the neighbouring waves through LDS (two slots, so one
 // barrier per half-step suffices).
-// MASK = false: every cell is updated; only for tiles whose region holds no
-// boundary cell of the array.  MASK = true: boundary cells keep their values;
-// any tile.  (One kernel with both paths needs more registers than either.)
-template <int W, int RPL, int MINW, bool MASK>
-__global__ void __launch_bounds__(64 * W, MINW) j2_kernel(J2Args a) {
-    constexpr int VEC = 2;
+// Loads read clamped rows and columns, so they need no guard: as in the row
+// march below, a value read for a cell outside the array only feeds boundary
+// cells, which are kept, or other cells outside.
+// Workgroups whose region holds a boundary cell of the array (uniform) run a
+// masked copy of the update, in which a boundary cell keeps the value its
+// array had one iteration ago, already in the register it is written to; the
+// others carry no mask.
+// Bound by FP64 issue (5 operations and two DPP moves per cell) on the
+// recomputed halo, then by the launch, loads and stores (about 4 us of a pass):
+// 1300^2 with 12 half-steps per pass takes 18.3 us per pass; one masked form
+// for every tile, 8 waves of 8 rows per lane, took 22.4.
+template <int RPL>
+__global__ void __launch_bounds__(1024, RPL <= 4 ? 8 : 4) j2_kernel(J2Args a) {
+    constexpr int VEC = 2, W = 16;
     constexpr int R = W * RPL, C = 64 * VEC;
     __shared__ double xch[2][W][2][C];
     // the wave index is uniform over a wave: say so, so that everything that
     // depends only on the row (bounds, masks, row addresses) stays scalar
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int tr, tc;
-    j2_tile(a, j_xcd_remap(blockIdx.x, gridDim.x), tr, tc);
+    // tiles run column by column, so a tile's upper and lower neighbours
+    // (whose halos it shares, the larger overlap) are recent in the same L2
+    const int b = j_xcd_remap(blockIdx.x, gridDim.x);
+    const int tr = b % a.tiles_r, tc = b / a.tiles_r;
     const int64_t n0 = a.n0;
     const int n1 = (int)a.n1;  // < 2^30, checked by the host
     const int ri0 = wave * RPL;
-    const int64_t gr = (int64_t)tr * a.inner_r - a.hh + ri0;  // global row of r = 0
-    const int gc = tc * a.inner_c - a.hh + lane * VEC;         // global column of v = 0
+    const int64_t gr0 = (int64_t)tr * a.inner_r - a.hh;  // global row of the region's first row
+    const int gc0 = tc * a.inner_c - a.hh;               // and column
+    const int64_t gr = gr0 + ri0;                        // global row of r = 0
+    const int gc = gc0 + lane * VEC;                     // global column of v = 0
+    const bool edge = gr0 <= 0 || gr0 + R >= n0 || gc0 <= 0 || gc0 + C >= n1;  // uniform over the workgroup
 
-    uint32_t rowin = 0, rowfix = 0;  // bit r: row in the array / a boundary row of the array
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int64_t i = gr + r;
-        if (i >= 0 && i < n0) rowin |= 1u << r;
-        if (i == 0 || i == n0 - 1) rowfix |= 1u << r;
-    }
-    unsigned colin = 0;
     uint64_t colfix[VEC];  // lanes whose column v is a boundary column of the array
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-        const int j = gc + v;
-        if (j >= 0 && j < n1) colin |= 1u << v;
-        colfix[v] = __builtin_amdgcn_ballot_w64(j == 0 || j == n1 - 1);
-    }
-    double va[RPL][VEC], vb[RPL][VEC];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int64_t i = gr + r;
-        const double *rowa = a.ain + i * n1;
-        const double *rowb = (a.phase ? a.bin : a.bfix) + i * n1;
-        const bool rfix = (rowfix >> r) & 1u;
+    for (int v = 0; v < VEC; ++v) colfix[v] = __builtin_amdgcn_ballot_w64(gc + v == 0 || gc + v == n1 - 1);
+    auto load = [&](const double *base, double(&x)[RPL][VEC]) __attribute__((always_inline)) {
+        const int c0 = min(max(gc, 0), n1 - 1), c1 = min(max(gc + 1, 0), n1 - 1), cp = min(max(gc, 0), n1 - 2);
+        auto row = [&](int r) { return base + min(max(gr + r, (int64_t)0), n0 - 1) * n1; };
         if (a.vec16) {
-            // both columns are in the array or neither (gc even, n1 even)
-            const bool in = ((rowin >> r) & 1u) && (colin & 1u);
-            const double2 x = in ? *reinterpret_cast<const double2 *>(rowa + (unsigned)gc) : double2{0.0, 0.0};
-            va[r][0] = x.x;
-            va[r][1] = x.y;
-        }
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const bool in = ((rowin >> r) & 1u) && ((colin >> v) & 1u);
-            const unsigned j = (unsigned)(gc + v);
-            const bool fixed = rfix || j == 0 || j == (unsigned)(n1 - 1);
-            if (!a.vec16) va[r][v] = in ? rowa[j] : 0.0;
-            vb[r][v] = (in && (a.phase || fixed)) ? rowb[j] : 0.0;
-        }
-    }
-
-    // Edge tiles: the values a half-step must keep.  Boundary rows are kept
-    // whole (skipped, a uniform branch); on other rows a lane holds at most
-    // one boundary-column cell (the array's first or last column, n1 >= 3
-    // when anything is updated), whose A and B values never change, so they
-    // are captured once here instead of keeping every old value alive.
-    double fixa[RPL], fixb[RPL];
-    if constexpr (MASK) {
+            for (int r = 0; r < RPL; ++r) {
+                const double2 y = *reinterpret_cast<const double2 *>(row(r) + cp);
+                x[r][0] = y.x;
+                x[r][1] = y.y;
+            }
+        } else {
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const bool v1 = (colfix[1] >> lane) & 1ull;
-            fixa[r] = v1 ? va[r][1] : va[r][0];
-            fixb[r] = v1 ? vb[r][1] : vb[r][0];
-        }
-    }
-
-    int slot = 0;
-    auto half = [&](double(&d)[RPL][VEC], const double(&s)[RPL][VEC], const double(&fix)[RPL],
-                    auto masked) __attribute__((always_inline)) {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            xch[slot][wave][0][lane * VEC + v] = s[0][v];
-            xch[slot][wave][1][lane * VEC + v] = s[RPL - 1][v];
-        }
-        __syncthreads();
-        const int wu = wave > 0 ? wave - 1 : 0, wd = wave < W - 1 ? wave + 1 : wave;
-        double up0[VEC], dn0[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            // the first and last waves read a slot of their own; the values
-            // only feed the region's edge rows
-            up0[v] = xch[slot][wu][1][lane * VEC + v];
-            dn0[v] = xch[slot][wd][0][lane * VEC + v];
-        }
-        slot ^= 1;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const double wl = from_lower(s[r][VEC - 1]);
-            const double er = from_upper(s[r][0]);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                const double c = s[r][v];
-                const double w = v == 0 ? wl : s[r][v > 0 ? v - 1 : 0];
-                const double e = v == VEC - 1 ? er : s[r][v < VEC - 1 ? v + 1 : v];
-                const double so = r == RPL - 1 ? dn0[v] : s[r < RPL - 1 ? r + 1 : r][v];
-                const double no = r == 0 ? up0[v] : s[r > 0 ? r - 1 : 0][v];
-                const double nv = kW2 * ((((c + w) + e) + so) + no);
-                if constexpr (decltype(masked)::value) {
-                    // a boundary row keeps all its cells (uniform branch), other
-                    // rows keep the lanes on a boundary column
-                    if (!((rowfix >> r) & 1u)) d[r][v] = j_keep(colfix[v], nv, fix[r]);
-                } else {
-                    d[r][v] = nv;
-                }
+            for (int r = 0; r < RPL; ++r) {
+                x[r][0] = row(r)[c0];
+                x[r][1] = row(r)[c1];
             }
         }
     };
-    auto steps = [&](auto masked) __attribute__((always_inline)) {
+    auto body = [&](auto masked) __attribute__((always_inline)) {
+        double va[RPL][VEC], vb[RPL][VEC];
+        load(a.ain, va);
+        // B: its own values when the pass starts with A, else only the boundary
+        // cells count (its interior is written before it is read)
+        if (a.phase || decltype(masked)::value) {
+            load(a.phase ? a.bin : a.bfix, vb);
+        } else {
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) vb[r][0] = vb[r][1] = 0.0;
+        }
+
+        int slot = 0;
+        auto half = [&](double(&d)[RPL][VEC], const double(&s)[RPL][VEC]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                xch[slot][wave][0][lane * VEC + v] = s[0][v];
+                xch[slot][wave][1][lane * VEC + v] = s[RPL - 1][v];
+            }
+            __syncthreads();
+            const int wu = wave > 0 ? wave - 1 : 0, wd = wave < W - 1 ? wave + 1 : wave;
+            double up0[VEC], dn0[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                // the first and last waves read a slot of their own; the values
+                // only feed the region's edge rows
+                up0[v] = xch[slot][wu][1][lane * VEC + v];
+                dn0[v] = xch[slot][wd][0][lane * VEC + v];
+            }
+            slot ^= 1;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const double wl = from_lower(s[r][VEC - 1]);
+                const double er = from_upper(s[r][0]);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const double c = s[r][v];
+                    const double w = v == 0 ? wl : s[r][v > 0 ? v - 1 : 0];
+                    const double e = v == VEC - 1 ? er : s[r][v < VEC - 1 ? v + 1 : v];
+                    const double so = r == RPL - 1 ? dn0[v] : s[r < RPL - 1 ? r + 1 : r][v];
+                    const double no = r == 0 ? up0[v] : s[r > 0 ? r - 1 : 0][v];
+                    const double nv = kW2 * ((((c + w) + e) + so) + no);
+                    if constexpr (decltype(masked)::value) {
+                        const int64_t i = gr + r;
+                        const uint64_t keep = (i == 0 || i == n0 - 1) ? ~(uint64_t)0 : colfix[v];
+                        d[r][v] = j_keep(keep, nv, d[r][v]);
+                    } else {
+                        d[r][v] = nv;
+                    }
+                }
+            }
+        };
         int s = 0;
         if (a.phase && a.nhalf > 0) {
-            half(va, vb, fixa, masked);
+            half(va, vb);
             s = 1;
         }
         for (; s + 2 <= a.nhalf; s += 2) {
-            half(vb, va, fixb, masked);
-            half(va, vb, fixa, masked);
+            half(vb, va);
+            half(va, vb);
         }
-        if (s < a.nhalf) half(vb, va, fixb, masked);
-    };
-    steps(std::integral_constant<bool, MASK>{});
+        if (s < a.nhalf) half(vb, va);
 
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int ri = ri0 + r;
-        if (ri < a.hh || ri >= R - a.hh || !((rowin >> r) & 1u)) continue;
-        const int64_t i = gr + r;
-        double *rowa = a.aout + i * n1;
-        double *rowb = a.bout + i * n1;
-        const bool binterior_row = i >= 1 && i <= n0 - 2;
-        // with vec16 both columns are inside the tile or neither (hh even)
-        if (a.vec16 && lane * VEC >= a.hh && lane * VEC < C - a.hh && (colin & 1u)) {
-            *reinterpret_cast<double2 *>(rowa + (unsigned)gc) = double2{va[r][0], va[r][1]};
-            if (a.write_b == 1) *reinterpret_cast<double2 *>(rowb + (unsigned)gc) = double2{vb[r][0], vb[r][1]};
-        }
+        for (int r = 0; r < RPL; ++r) {
+            const int ri = ri0 + r;
+            const int64_t i = gr + r;
+            if (ri < a.hh || ri >= R - a.hh || i >= n0) continue;  // (i >= 0 from ri >= hh)
+            double *rowa = a.aout + i * n1;
+            double *rowb = a.bout + i * n1;
+            const bool binterior_row = i >= 1 && i <= n0 - 2;
+            // with vec16 both columns are inside the tile or neither (hh even)
+            if (a.vec16 && lane * VEC >= a.hh && lane * VEC < C - a.hh && gc < n1) {
+                *reinterpret_cast<double2 *>(rowa + (unsigned)gc) = double2{va[r][0], va[r][1]};
+                if (a.write_b == 1) *reinterpret_cast<double2 *>(rowb + (unsigned)gc) = double2{vb[r][0], vb[r][1]};
+            }
+            if (a.vec16 && a.write_b != 2) continue;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const int ci = lane * VEC + v;
-            if (ci < a.hh || ci >= C - a.hh || !((colin >> v) & 1u)) continue;
-            const unsigned j = (unsigned)(gc + v);
-            if (!a.vec16) rowa[j] = va[r][v];
-            if ((a.write_b == 1 && !a.vec16) ||
-                (a.write_b == 2 && binterior_row && j >= 1 && j <= (unsigned)(n1 - 2)))
-                rowb[j] = vb[r][v];
+            for (int v = 0; v < VEC; ++v) {
+                const int ci = lane * VEC + v;
+                if (ci < a.hh || ci >= C - a.hh || gc + v >= n1) continue;
+                const unsigned j = (unsigned)(gc + v);
+                if (!a.vec16) rowa[j] = va[r][v];
+                if ((a.write_b == 1 && !a.vec16) ||
+                    (a.write_b == 2 && binterior_row && j >= 1 && j <= (unsigned)(n1 - 2)))
+                    rowb[j] = vb[r][v];
+            }
         }
-    }
+    };
+    if (edge) body(std::true_type{});
+    else body(std::false_type{});
 }
 
 // ------------------------------------------- jacobi_2d, marching down rows
@@ -630,38 +577,38 @@ int j1_pick_k(int64_t n, int64_t hh) {
     return 32;
 }
 
-// 2D workgroup shapes: (waves, rows per lane), all within the 128 VGPRs of
-// four waves per SIMD without spilling (a kernel holding both the masked and
-// the unmasked update spilled about 64 bytes per lane, which at 46800^2
-// wrote about 15 GB per pass to HBM; hence one instantiation per path).
-struct J2Cfg {
-    int w, rpl;
-};
-constexpr J2Cfg kJ2Cfgs[] = {{16, 4}, {8, 8}, {16, 8}};
-
-// Launch plan of a 2D pass: a shape and whether the pass is split into the
-// ring of edge tiles (masked) and the interior rectangle (unmasked, two
-// launches) or run as one masked launch.  Measured at T=1000: large arrays
-// (46800^2: 1834 vs 1554 GLUP/s) gain from the split with 16 x 4; small ones
-// (1300^2, a fifth of the tiles in the ring, launch-bound) run best as one
-// launch of 8 x 8.  DCP_J2_CFG / DCP_J2_MODE (1 = one launch, 2 = split)
-// force the choice (tuning runs only).
-struct J2Plan {
-    int cfg;
-    bool split;
-};
-
-int64_t j2_interior_tiles(int64_t n0, int64_t n1, int64_t hh, int rows, int64_t *all) {
-    const int64_t ir = rows - 2 * hh, ic = 128 - 2 * hh;
-    const int64_t tr = (n0 + ir - 1) / ir, tc = (n1 + ic - 1) / ic;
-    *all = tr * tc;
-    auto span = [&](int64_t n, int64_t inner, int extent, int64_t tiles) {
-        const int64_t lo = (hh + 1 + inner - 1) / inner;
-        const int64_t num = n - 2 - (extent - 1) + hh;
-        const int64_t hi = num < 0 ? -1 : std::min<int64_t>(num / inner, tiles - 1);
-        return hi >= lo ? hi - lo + 1 : 0;
-    };
-    return span(n0, ir, rows, tr) * span(n1, ic, 128, tc);
+// Rows per lane of the 2D region tiles (16 waves, so 32 to 128 rows of 128
+// columns): the choice with the least work for the busiest CU, in rows of a
+// tile, halo rows included.  A pass costs about 28 rows' worth per tile for
+// the launch, loads and stores.  Tiles of up to four rows per lane (64 VGPRs)
+// run two to a CU and hide that behind each other's updates, the more so over
+// several rounds.  Measured with 12 half-steps, us per pass: 300^2 8.1 with
+// two rows per lane, 12.0 with four, 20.9 with eight; 1300^2 18.3 with six
+// (247 tiles), 19.5 with four (429), 19.7 with three; 2000^2 33 with four,
+// 39 with seven; 5001 x 4999 181 with four, 218 with seven.  DCP_J2_CFG = 0,
+// 1 or 2 forces 4, 6 or 8 rows per lane where the halo leaves a tile (tuning
+// runs only).
+int j2_pick_rpl(int64_t n0, int64_t n1, int64_t hh) {
+    const char *fc = dcp::tuning_env("DCP_J2_CFG");
+    if (fc && *fc) {
+        const int c = std::atoi(fc);
+        if (c >= 0 && c < 3 && 16 * (4 + 2 * c) > 2 * hh) return 4 + 2 * c;
+    }
+    int best = 8;
+    double cost = 1e300;
+    for (int rpl = 2; rpl <= 8; ++rpl) {
+        const int64_t rows = 16 * rpl, inner_r = rows - 2 * hh, inner_c = kJ2C - 2 * hh;
+        if (inner_r <= 0) continue;
+        const double tiles = (double)((n0 + inner_r - 1) / inner_r) * (double)((n1 + inner_c - 1) / inner_c);
+        const double per_cu = std::ceil(tiles / 256.0);
+        const double x = rpl > 4 ? per_cu * (double)(rows + 28)
+                                 : per_cu <= 2.0 ? per_cu * (double)rows + 28.0 : 0.87 * per_cu * (double)rows;
+        if (x < cost) {
+            cost = x;
+            best = rpl;
+        }
+    }
+    return best;
 }
 
 // The row-marching form (j2m_kernel): used for arrays that give it at least
@@ -698,21 +645,6 @@ J2MPlan j2m_pick(int64_t n0, int64_t n1, int64_t hh) {
     const char *fm = dcp::tuning_env("DCP_J2_MODE");
     if (fm && *fm) m.use = std::atoi(fm) == 3;
     return m;
-}
-
-J2Plan j2_pick(int64_t n0, int64_t n1, int64_t hh) {
-    J2Plan p{1, false};
-    int64_t all = 0;
-    const int64_t in = j2_interior_tiles(n0, n1, hh, kJ2Cfgs[0].w * kJ2Cfgs[0].rpl, &all);
-    if (all >= 2048 && in * 10 >= all * 9) p = J2Plan{0, true};
-    const char *fc = dcp::tuning_env("DCP_J2_CFG");
-    if (fc && *fc) {
-        const int c = std::atoi(fc);
-        if (c >= 0 && c < 3 && kJ2Cfgs[c].w * kJ2Cfgs[c].rpl > 2 * hh) p.cfg = c;
-    }
-    const char *fm = dcp::tuning_env("DCP_J2_MODE");
-    if (fm && *fm) p.split = std::atoi(fm) == 2;
-    return p;
 }
 
 template <int K>
@@ -918,46 +850,21 @@ int dcp_jacobi_2d(int32_t tsteps, double *A, double *B, int64_t n0, int64_t n1, 
     const JPlan p = j_plan(g, tsteps, hp);
     st = j_check_buffers(g, A, B, ws, ws_bytes, j_ws_need(g, p));
     if (st != DCP_OK || p.passes == 0) return st;
-    const J2Plan plan = j2_pick(n0, n1, p.hh);
-    const int cfg = plan.cfg;
-    const int rows = kJ2Cfgs[cfg].w * kJ2Cfgs[cfg].rpl;
-    const int inner_r = rows - 2 * (int)p.hh, inner_c = kJ2C - 2 * (int)p.hh;
+    const int rpl = j2_pick_rpl(n0, n1, p.hh);
+    const int inner_r = 16 * rpl - 2 * (int)p.hh, inner_c = kJ2C - 2 * (int)p.hh;
     const int64_t tiles_r = (n0 + inner_r - 1) / inner_r, tiles_c = (n1 + inner_c - 1) / inner_c;
     if (tiles_c > INT32_MAX || tiles_r > INT32_MAX / tiles_c) return DCP_E_SHAPE;
-    // interior rectangle: tiles whose region [t*inner - hh, t*inner - hh + extent)
-    // lies in [1, n - 2] on both axes
-    auto lo_hi = [&](int64_t n, int inner, int extent, int64_t tiles, int &lo, int &hi) {
-        lo = (int)((p.hh + 1 + inner - 1) / inner);
-        const int64_t num = n - 2 - (extent - 1) + p.hh;
-        hi = num < 0 ? -1 : (int)std::min<int64_t>(num / inner, tiles - 1);
-    };
-    int r_lo, r_hi, c_lo, c_hi;
-    lo_hi(n0, inner_r, rows, tiles_r, r_lo, r_hi);
-    lo_hi(n1, inner_c, kJ2C, tiles_c, c_lo, c_hi);
-    if (r_lo > r_hi || c_lo > c_hi) {  // no interior tile: everything is ring
-        r_lo = (int)tiles_r;
-        r_hi = (int)tiles_r - 1;
-        c_lo = 0;
-        c_hi = -1;
-    }
-    const int64_t n_in = (int64_t)(r_hi - r_lo + 1) * (c_hi >= c_lo ? c_hi - c_lo + 1 : 0);
-    const int64_t n_all = tiles_r * tiles_c, n_ring = n_all - n_in;
-    // one masked launch over all tiles, or the ring (masked) and the interior
-    // rectangle (unmasked) as two launches
-    const bool split = plan.split && n_in > 0;
     hipStream_t sm = static_cast<hipStream_t>(stream);
-    auto launch_set = [&](J2Args a, int set, int64_t blocks, bool mask) -> hipError_t {
-        a.set = set;
-        const dim3 grid((unsigned)blocks);
-        if (cfg == 1) {
-            if (mask) hipLaunchKernelGGL((j2_kernel<8, 8, 4, true>), grid, dim3(512), 0, sm, a);
-            else hipLaunchKernelGGL((j2_kernel<8, 8, 4, false>), grid, dim3(512), 0, sm, a);
-        } else if (cfg == 2) {
-            if (mask) hipLaunchKernelGGL((j2_kernel<16, 8, 4, true>), grid, dim3(1024), 0, sm, a);
-            else hipLaunchKernelGGL((j2_kernel<16, 8, 4, false>), grid, dim3(1024), 0, sm, a);
-        } else {
-            if (mask) hipLaunchKernelGGL((j2_kernel<16, 4, 4, true>), grid, dim3(1024), 0, sm, a);
-            else hipLaunchKernelGGL((j2_kernel<16, 4, 4, false>), grid, dim3(1024), 0, sm, a);
+    auto launch_tiles = [&](const J2Args &a) -> hipError_t {
+        const dim3 grid((unsigned)(tiles_r * tiles_c)), block(1024);
+        switch (rpl) {
+            case 2: hipLaunchKernelGGL(j2_kernel<2>, grid, block, 0, sm, a); break;
+            case 3: hipLaunchKernelGGL(j2_kernel<3>, grid, block, 0, sm, a); break;
+            case 4: hipLaunchKernelGGL(j2_kernel<4>, grid, block, 0, sm, a); break;
+            case 5: hipLaunchKernelGGL(j2_kernel<5>, grid, block, 0, sm, a); break;
+            case 6: hipLaunchKernelGGL(j2_kernel<6>, grid, block, 0, sm, a); break;
+            case 7: hipLaunchKernelGGL(j2_kernel<7>, grid, block, 0, sm, a); break;
+            default: hipLaunchKernelGGL(j2_kernel<8>, grid, block, 0, sm, a); break;
         }
         return hipGetLastError();
     };
@@ -989,14 +896,8 @@ int dcp_jacobi_2d(int32_t tsteps, double *A, double *B, int64_t n0, int64_t n1, 
                                 return launch_march(m, nh);
                             }
                             const J2Args a{ain, bin, bfix, aout, bout, n0, n1, inner_r, inner_c,
-                                           (int)tiles_r, (int)tiles_c, (int)p.hh, nh, ph, wb, v16 ? 1 : 0,
-                                           0, r_lo, r_hi, c_lo, c_hi};
-                            if (!split) return launch_set(a, 0, n_all, true);
-                            if (n_ring > 0) {
-                                const hipError_t e = launch_set(a, 2, n_ring, true);
-                                if (e != hipSuccess) return e;
-                            }
-                            return launch_set(a, 1, n_in, false);
+                                           (int)tiles_r, (int)p.hh, nh, ph, wb, v16 ? 1 : 0};
+                            return launch_tiles(a);
                         });
 }
 

@@ -121,6 +121,19 @@ def test_jacobi_2d_marching_form(monkeypatch, shape, tsteps, tblock, cfg):
     assert_same(gpu_run(2, tsteps, A, B, tblock), oracle.jacobi_2d(tsteps, A, B), "jacobi_2d marching")
 
 
+# each number of rows per lane the region tiles choose by themselves (2 to 8;
+# 1400 x 1400 with 12 half-steps: 7), odd and even rows, passes that start
+# with A (tblock 1 and odd ones)
+@pytest.mark.parametrize("shape,tblock", [((410, 131), 12), ((700, 131), 12), ((775, 777), 12), ((1005, 1004), 12),
+                                          ((1201, 1199), 12), ((1400, 1400), 12), ((1500, 1501), 12), ((33, 1000), 16),
+                                          ((515, 300), 1), ((515, 301), 3)])
+def test_jacobi_2d_region_tile_heights(shape, tblock):
+    A, B = inputs.jacobi_fields(2, shape[0], seed=5, n1=shape[1])
+    for tsteps in (2, 15):
+        say(f"jacobi_2d tile heights shape={shape} tsteps={tsteps} tblock={tblock}")
+        assert_same(gpu_run(2, tsteps, A, B, tblock), oracle.jacobi_2d(tsteps, A, B), "jacobi_2d tile heights")
+
+
 @pytest.mark.parametrize("shape,tblock", [((400, 484), 16), ((401, 566), 8), ((257, 388), 16), ((193, 674), 10),
                                           ((130, 416), 4)])
 def test_jacobi_2d_marching_tile_order(monkeypatch, shape, tblock):
