@@ -89,33 +89,50 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
     return t;
 }
 
-// Tile for one field operand layout.  The default is tuned for the 512^3
-// class of grids; DCP_TILE_SHAPE / DCP_TILE_ZC override it in tuning runs
-// (with DCP_TUNING=1).
-Tile pick_tile(int dtype, const Geo &g, bool vec_ok) {
+// Tile of the one-step kernels.  Two rows per lane (shape 1) and short z-runs:
+// 8 planes, fewer where that leaves under 2048 workgroups, down to 2, and to 1
+// under 512; the planes a run shares with the next come from the XCD's L2,
+// and the many short workgroups keep every CU busy to the end.  Measured, us
+// per step with norms, against four rows per lane with runs of 8 to 64
+// planes: FP64 64^3 4.9 / 12.2, 96^3 7.8 / 14.1, 128^3 12.8 / 17.9, 192^3
+// 39.5 / 48.2, 256^3 74 / 79, 512^3 559 / 592; FP32 128^3 8.8 / 17.5, 512^3
+// 280 / 288.  `most` bounds the workgroups (their partial sums): the run
+// grows past it, up to 64 planes, and then the tile to four rows per lane.
+// DCP_TILE_SHAPE / DCP_TILE_ZC override the choice in tuning runs (with
+// DCP_TUNING=1).
+Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
     const int wide = dtype == DCP_F64 ? 2 : 4;
     const int vec = vec_ok ? wide : 1;
-    int shape = env_int("DCP_TILE_SHAPE", 0);
-    if (shape < 0 || shape >= num_shapes()) shape = 0;
+    int shape = env_int("DCP_TILE_SHAPE", -1);
+    const bool forced = shape >= 0 && shape < num_shapes();
+    if (!forced) shape = 1;
     int zc = env_int("DCP_TILE_ZC", 0);
     if (zc <= 0) {
-        // enough workgroups to fill 256 CUs several times over, but long
-        // z-runs so the two extra planes per run stay a small overhead
-        zc = 64;
-        while (zc > 8 && make_tile(g, vec, shape, zc).nblk >= 0 &&
-               make_tile(g, vec, shape, zc).nblk < 2048)
-            zc /= 2;
+        auto blocks = [&](int z) {
+            const int nb = make_tile(g, vec, shape, z).nblk;
+            return nb < 0 ? INT32_MAX : nb;
+        };
+        zc = 8;
+        while (zc > 2 && blocks(zc) < 2048) zc /= 2;
+        if (zc == 2 && blocks(2) < 512) zc = 1;
+        while (zc < 64 && blocks(zc) > most) zc *= 2;
+        if (!forced && blocks(zc) > most) shape = 0;
     }
     if (g.nz > 0 && zc > g.nz) zc = (int)g.nz;
     if (zc < 1) zc = 1;
     return make_tile(g, vec, shape, zc);
 }
 
+// Most workgroups of a step that is called by itself (one reduction of that
+// many pairs; without norms there is none) and of each step of a run, whose
+// workspace holds every step's pairs.
+constexpr int kStepBlocks = 8192, kRunBlocks = 4096, kPlainBlocks = 32768;
+
 // Largest workgroup count over both vector widths (workspace sizing must not
 // depend on pointer alignment).
-int max_blocks(int dtype, const Geo &g) {
+int max_blocks(int dtype, const Geo &g, int most) {
     if (g.n == 0) return 0;
-    const Tile a = pick_tile(dtype, g, true), b = pick_tile(dtype, g, false);
+    const Tile a = pick_tile(dtype, g, true, most), b = pick_tile(dtype, g, false, most);
     if (a.nblk < 0 || b.nblk < 0) return -1;
     return a.nblk > b.nblk ? a.nblk : b.nblk;
 }
@@ -134,7 +151,7 @@ int layout_step(int dtype, int impl, const Geo &g, bool norms, StepWs *w) {
         off += 3 * align_up(g.bytes());
     }
     if (norms && g.n > 0) {
-        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g);
+        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kStepBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         w->partials = off;
         off += align_up((size_t)nb * 2 * sizeof(double));
@@ -200,7 +217,7 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
         off += 3 * align_up(g.bytes());
     }
     if (norms) {
-        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g);
+        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kRunBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (impl == DCP_FUSED && tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) &&
@@ -237,7 +254,7 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         return DCP_OK;
     }
     if (g.n > 0) {
-        int nb = max_blocks(dtype, g);
+        int nb = max_blocks(dtype, g, kRunBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) && tb.nblk > nb) nb = tb.nblk;
@@ -482,13 +499,14 @@ int step_common(int impl, int dtype, const void *u, const void *f, void *u_out, 
 
     double *partials = norms2 ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
     if (impl == DCP_FUSED) {
-        const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}));
+        const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}),
+                                norms2 ? kStepBlocks : kPlainBlocks);
         DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, u, f, u_out, partials, st));
         if (norms2) DCP_TRY(launch_finalize(partials, t.nblk, t.nblk, 1, norms2, nullptr, 0, st));
     } else {
         void *tmp[3] = {at(ws, w.temps), at(ws, w.temps + align_up(fb)), at(ws, w.temps + 2 * align_up(fb))};
         const bool vok = vec_ok_for(dtype, g, {u, f, u_out, tmp[0], tmp[1], tmp[2]});
-        const Tile t = pick_tile(dtype, g, vok);
+        const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
         DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, vok, u, f, u_out, tmp, partials, st));
         if (norms2) {
             const int nb = ew_norm_blocks(g.n);
@@ -519,7 +537,7 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         return DCP_OK;
     }
     const size_t fb = align_up(g.bytes());
-    const int nb = max_blocks(dtype, g);
+    const int nb = max_blocks(dtype, g, kRunBlocks);
     if (nb < 0) return DCP_E_SHAPE;
     w->nblk = nb;
     w->origin = off;
@@ -746,7 +764,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     auto slot = [&](int32_t c) { return static_cast<void *>(static_cast<char *>(ckpt) + (size_t)c * fb); };
     bool vok = vec_ok_for(dtype, g, {u, f, buf, tmp[0], tmp[1], tmp[2]});
     for (int32_t c = 0; c < nslots; ++c) vok = vok && aligned16(slot(c));
-    const Tile t = pick_tile(dtype, g, vok);
+    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
     const int nblk_one = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : t.nblk;
     const int stride = w.nblk;  // partial slots per step (>= every kernel's workgroup count)
     double *partials = norms ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
@@ -898,7 +916,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     if (lsum) vok = vok && aligned16(lsum);
     for (int32_t c = 0; c < nslots; ++c) vok = vok && aligned16(slot(c));
     for (int32_t j = 0; j + 1 < kk; ++j) vok = vok && aligned16(seg(j));
-    const Tile t = pick_tile(dtype, g, vok);
+    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
     double *sums = reinterpret_cast<double *>(at(ws, w.sums));
     const int stride = w.nblk;
@@ -1050,7 +1068,7 @@ int dcp_revolve_forward(int dtype, void *u, const void *f, int64_t nx, int64_t n
     void *scratch = at(ws, w.scratch);
     bool vok = vec_ok_for(dtype, g, {u, f, B.buf(kRvOrigin), B.buf(nslots), scratch});
     for (int32_t i = 0; i < nslots; ++i) vok = vok && aligned16(B.buf(i));
-    const Tile t = pick_tile(dtype, g, vok);
+    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, B.buf(kRvOrigin), 0.0, g.n, vok, st));
@@ -1117,7 +1135,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, grad_f, B.buf(kRvOrigin), B.buf(nslots), scratch,
                                      lam[0], lam[1], lsum});
     for (int32_t i = 0; i < nslots; ++i) vok = vok && aligned16(B.buf(i));
-    const Tile t = pick_tile(dtype, g, vok);
+    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
