@@ -188,11 +188,12 @@ int dcp_step_unfused(int dtype, const void *u, const void *f, void *u_out,
  *   T           >= 0 (T = 0 leaves u unchanged)
  *   tblock      most steps fused per pass over memory (temporal blocking),
  *               1, 2 or 3; 1 = one pass per step.  Values > 1 need impl =
- *               DCP_FUSED and 16-byte aligned fields with nx a multiple of
- *               the 16-byte vector (2 doubles, 4 floats).  Passes of tblock
- *               steps run on tiles of whole x-rows, or of x-segments with a
- *               halo of recomputed points when rows are too long for a
- *               whole-row tile; T mod tblock remaining steps run as shorter
+ *               DCP_FUSED.  Passes of tblock steps run on tiles of whole
+ *               x-rows, or of x-segments with a halo of recomputed points
+ *               (long rows; rows that are not whole 16-byte vectors of 2
+ *               doubles or 4 floats, on grids of at least 2^18 points: below
+ *               that, and where no tile fits, single steps are as fast);
+ *               T mod tblock remaining steps run as shorter
  *               passes (dcp_run_plan reports the passes).  Either way every
  *               point is computed with the same operations, so u_T is
  *               bitwise the same for every tblock.
@@ -211,8 +212,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx,
             void *stream);
 
 /*
- * How a dcp_run with these arguments takes its steps, for 16-byte aligned
- * fields (what torch and hipMalloc return): passes over memory of one, two
+ * How a dcp_run with these arguments takes its steps: passes over memory of one, two
  * and three steps, so that a caller can see when a grid falls back to
  * shorter passes.  Host only; asks the current device for its LDS size when
  * there is one.  Writes *info (a host pointer); argument errors as dcp_run.

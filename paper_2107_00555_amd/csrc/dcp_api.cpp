@@ -96,8 +96,8 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
 // per step with norms, against four rows per lane with runs of 8 to 64
 // planes: FP64 64^3 4.9 / 12.2, 96^3 7.8 / 14.1, 128^3 12.8 / 17.9, 192^3
 // 39.5 / 48.2, 256^3 74 / 79, 512^3 559 / 592; FP32 128^3 8.8 / 17.5, 512^3
-// 280 / 288.  `most` bounds the workgroups (their partial sums): the run
-// grows past it, up to 64 planes, and then the tile to four rows per lane.
+// 280 / 288.  `most` bounds the workgroups (their partial sums): past it the
+// tile takes four rows per lane, then longer runs, up to 64 planes.
 // DCP_TILE_SHAPE / DCP_TILE_ZC override the choice in tuning runs (with
 // DCP_TUNING=1).
 Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
@@ -115,18 +115,17 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
         zc = 8;
         while (zc > 2 && blocks(zc) < 2048) zc /= 2;
         if (zc == 2 && blocks(2) < 512) zc = 1;
-        while (zc < 64 && blocks(zc) > most) zc *= 2;
         if (!forced && blocks(zc) > most) shape = 0;
+        while (zc < 64 && blocks(zc) > most) zc *= 2;
     }
     if (g.nz > 0 && zc > g.nz) zc = (int)g.nz;
     if (zc < 1) zc = 1;
     return make_tile(g, vec, shape, zc);
 }
 
-// Most workgroups of a step that is called by itself (one reduction of that
-// many pairs; without norms there is none) and of each step of a run, whose
-// workspace holds every step's pairs.
-constexpr int kStepBlocks = 8192, kRunBlocks = 4096, kPlainBlocks = 32768;
+// Most workgroups of a step whose sums are reduced (a run's workspace holds
+// every step's pairs), and of one without.
+constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
 
 // Largest workgroup count over both vector widths (workspace sizing must not
 // depend on pointer alignment).
@@ -151,7 +150,7 @@ int layout_step(int dtype, int impl, const Geo &g, bool norms, StepWs *w) {
         off += 3 * align_up(g.bytes());
     }
     if (norms && g.n > 0) {
-        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kStepBlocks);
+        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         w->partials = off;
         off += align_up((size_t)nb * 2 * sizeof(double));
@@ -217,7 +216,7 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
         off += 3 * align_up(g.bytes());
     }
     if (norms) {
-        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kRunBlocks);
+        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (impl == DCP_FUSED && tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) &&
@@ -254,7 +253,7 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         return DCP_OK;
     }
     if (g.n > 0) {
-        int nb = max_blocks(dtype, g, kRunBlocks);
+        int nb = max_blocks(dtype, g, kSumBlocks);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) && tb.nblk > nb) nb = tb.nblk;
@@ -397,6 +396,11 @@ bool plan_tbk(int dtype, const Geo &g, int B, bool vok, TbkTile *t) {
     return tbk_for(dtype, g, B, vok, device_lds(), t);
 }
 
+// Smallest ragged grid that takes passes of several steps: at 64^3 points a
+// three-step pass takes as long as three single steps (17 us against 18), at
+// 101 x 97 x 103 23 us against 26, at 257 x 263 x 255 98 against 290.
+constexpr int64_t kRaggedMin = (int64_t)1 << 18;
+
 // The passes of a fused dcp_run: three steps where tblock >= 3 and the
 // B-step kernel applies; two steps over whole rows where the two-step kernel
 // applies, else over x-segments; one step otherwise and for the remainders.
@@ -419,7 +423,10 @@ PassPlan plan_passes(int dtype, int impl, const Geo &g, int32_t T, int32_t tbloc
                      int stride) {
     PassPlan pp;
     if (impl != DCP_FUSED) return pp;
-    pp.use_tb = T >= 2 && plan_tb(dtype, g, tblock, vok, &pp.tb) && (!norms || pp.tb.nblk <= stride);
+    // ragged rows (not whole vectors): over x-segments, on grids that are worth it
+    const bool ragged = g.nx % (dtype == DCP_F64 ? 2 : 4) != 0;
+    if (ragged && g.n < kRaggedMin) return pp;
+    pp.use_tb = T >= 2 && !ragged && plan_tb(dtype, g, tblock, vok, &pp.tb) && (!norms || pp.tb.nblk <= stride);
     pp.use_k2 = !pp.use_tb && T >= 2 && tblock >= 2 && plan_tbk(dtype, g, 2, vok, &pp.k2) &&
                 (!norms || pp.k2.nblk <= stride);
     pp.use_k3 = T >= 3 && tblock >= 3 && plan_tbk(dtype, g, 3, vok, &pp.k3) && (!norms || pp.k3.nblk <= stride);
@@ -450,6 +457,7 @@ hipError_t tbk_fwd_pass(int dtype, int bc, const Geo &g, const dcp_coeffs &c, co
     a.halo = tk.halo;
     a.chf = tk.chf;
     a.sblk = tk.sblk;
+    a.shift = tk.shift;
     return launch_tbk(dtype, bc, part != nullptr, tk, a, st);
 }
 
@@ -466,9 +474,17 @@ hipError_t fwd_pass(int dtype, int bc, const Geo &g, const dcp_coeffs &c, const 
     return fused_step(dtype, bc, g, c, t, u, f, out, nullptr, st);
 }
 
+// 16-byte lanes of the stencil kernels: rows of at least one vector, pointers
+// aligned to their elements (global vectors need no more).
 bool vec_ok_for(int dtype, const Geo &g, std::initializer_list<const void *> ptrs) {
-    const int wide = dtype == DCP_F64 ? 2 : 4;
-    if (g.nx % wide != 0) return false;
+    if (g.nx < (dtype == DCP_F64 ? 2 : 4)) return false;
+    for (const void *p : ptrs)
+        if ((uintptr_t)p % g.esz != 0) return false;
+    return true;
+}
+
+// The element-wise kernels run over the flat field: 16-byte aligned pointers.
+bool ew_ok(std::initializer_list<const void *> ptrs) {
     for (const void *p : ptrs)
         if (p && !aligned16(p)) return false;
     return true;
@@ -500,14 +516,15 @@ int step_common(int impl, int dtype, const void *u, const void *f, void *u_out, 
     double *partials = norms2 ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
     if (impl == DCP_FUSED) {
         const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}),
-                                norms2 ? kStepBlocks : kPlainBlocks);
+                                norms2 ? kSumBlocks : kPlainBlocks);
         DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, u, f, u_out, partials, st));
         if (norms2) DCP_TRY(launch_finalize(partials, t.nblk, t.nblk, 1, norms2, nullptr, 0, st));
     } else {
         void *tmp[3] = {at(ws, w.temps), at(ws, w.temps + align_up(fb)), at(ws, w.temps + 2 * align_up(fb))};
         const bool vok = vec_ok_for(dtype, g, {u, f, u_out, tmp[0], tmp[1], tmp[2]});
-        const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
-        DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, vok, u, f, u_out, tmp, partials, st));
+        const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+        const bool eok = ew_ok({u, f, u_out, tmp[0], tmp[1], tmp[2]});
+        DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, eok, u, f, u_out, tmp, partials, st));
         if (norms2) {
             const int nb = ew_norm_blocks(g.n);
             DCP_TRY(launch_finalize(partials, nb, nb, 1, norms2, nullptr, 0, st));
@@ -537,7 +554,7 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         return DCP_OK;
     }
     const size_t fb = align_up(g.bytes());
-    const int nb = max_blocks(dtype, g, kRunBlocks);
+    const int nb = max_blocks(dtype, g, kSumBlocks);
     if (nb < 0) return DCP_E_SHAPE;
     w->nblk = nb;
     w->origin = off;
@@ -762,9 +779,10 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     if (impl == DCP_UNFUSED)
         for (int i = 0; i < 3; ++i) tmp[i] = at(ws, w.temps + i * align_up(fb));
     auto slot = [&](int32_t c) { return static_cast<void *>(static_cast<char *>(ckpt) + (size_t)c * fb); };
-    bool vok = vec_ok_for(dtype, g, {u, f, buf, tmp[0], tmp[1], tmp[2]});
-    for (int32_t c = 0; c < nslots; ++c) vok = vok && aligned16(slot(c));
-    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
+    const bool vok = vec_ok_for(dtype, g, {u, f, buf, tmp[0], tmp[1], tmp[2], ckpt});
+    bool eok = ew_ok({u, f, buf, tmp[0], tmp[1], tmp[2]});  // of every state and temporary
+    for (int32_t c = 0; c < nslots; ++c) eok = eok && aligned16(slot(c));
+    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
     const int nblk_one = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : t.nblk;
     const int stride = w.nblk;  // partial slots per step (>= every kernel's workgroup count)
     double *partials = norms ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
@@ -782,7 +800,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     if (norms) step_nblk.assign((size_t)T, nblk_one);
 
     auto is_ckpt = [&](int32_t t) { return nslots > 0 && t % ckpt_every == 0 && t / ckpt_every < nslots; };
-    if (nslots > 0) DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, slot(0), 0.0, g.n, vok, st));
+    if (nslots > 0) DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, slot(0), 0.0, g.n, ew_ok({u, slot(0)}), st));
     const void *cur = u;
     for (int32_t s = 0; s < T;) {
         const int32_t len = pp.len_at(s, T);
@@ -807,12 +825,12 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
         } else if (impl == DCP_FUSED) {
             DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, cur, f, nxt, p, st));
         } else {
-            DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, vok, cur, f, nxt, tmp, p, st));
+            DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, eok, cur, f, nxt, tmp, p, st));
         }
         cur = nxt;
         s = se;
     }
-    if (cur != u) DCP_TRY(launch_ew(dtype, EW_COPY, cur, nullptr, u, 0.0, g.n, vok, st));
+    if (cur != u) DCP_TRY(launch_ew(dtype, EW_COPY, cur, nullptr, u, 0.0, g.n, ew_ok({cur, u}), st));
     if (norms) {
         // one fixed-order reduction per run of steps that share a workgroup count
         for (int32_t s0 = 0; s0 < T;) {
@@ -840,7 +858,7 @@ int dcp_run_plan(int dtype, int impl, int64_t nx, int64_t ny, int64_t nz, int32_
     std::memset(info, 0, sizeof(*info));
     if (T == 0 || g.n == 0) return DCP_OK;
     const int wide = dtype == DCP_F64 ? 2 : 4;
-    const PassPlan pp = plan_passes(dtype, impl, g, T, tblock, g.nx % wide == 0, norms != 0, w.nblk);
+    const PassPlan pp = plan_passes(dtype, impl, g, T, tblock, g.nx >= wide, norms != 0, w.nblk);
     int32_t most = 0;
     for (int32_t s = 0; s < T;) {
         const int32_t len = pp.len_at(s, T);
@@ -898,9 +916,9 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     if (T == 0 || g.n == 0) {
         if (g.n > 0)
             DCP_TRY(launch_ew(dtype, EW_COPY, lam_T, nullptr, grad_u0, 0.0, g.n,
-                              vec_ok_for(dtype, g, {lam_T, grad_u0}), st));
+                              ew_ok({lam_T, grad_u0}), st));
         if (grad_f && g.n > 0)
-            DCP_TRY(launch_ew(dtype, EW_ZERO, nullptr, nullptr, grad_f, 0.0, g.n, vec_ok_for(dtype, g, {grad_f}), st));
+            DCP_TRY(launch_ew(dtype, EW_ZERO, nullptr, nullptr, grad_f, 0.0, g.n, ew_ok({grad_f}), st));
         DCP_TRY(launch_zero(grad_ab, 2, st));
         if (grad_gamma) DCP_TRY(launch_zero(grad_gamma, 1, st));
         return DCP_OK;
@@ -912,11 +930,8 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     const int32_t kk = ckpt_every < T ? ckpt_every : T;
     auto seg = [&](int32_t j) { return static_cast<void *>(at(ws, w.seg + (size_t)j * align_up(fb))); };
     auto slot = [&](int32_t c) { return static_cast<const void *>(static_cast<const char *>(ckpt) + (size_t)c * fb); };
-    bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, lam[0], lam[1]});
-    if (lsum) vok = vok && aligned16(lsum);
-    for (int32_t c = 0; c < nslots; ++c) vok = vok && aligned16(slot(c));
-    for (int32_t j = 0; j + 1 < kk; ++j) vok = vok && aligned16(seg(j));
-    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
+    const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, lam[0], lam[1], lsum, ckpt, seg(0)});
+    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
     double *sums = reinterpret_cast<double *>(at(ws, w.sums));
     const int stride = w.nblk;
@@ -1020,13 +1035,13 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
             double *dp = reinterpret_cast<double *>(at(ws, w.dot));
             const int nb = ew_norm_blocks(g.n);
             double *pair = dp + 2 * (size_t)nb;
-            DCP_TRY(launch_ew_dot(dtype, lsum, f, dp, g.n, vec_ok_for(dtype, g, {lsum, f}), st));
+            DCP_TRY(launch_ew_dot(dtype, lsum, f, dp, g.n, ew_ok({lsum, f}), st));
             DCP_TRY(launch_finalize(dp, nb, nb, 1, pair, nullptr, 0, st));
             DCP_TRY(launch_scalar_scale(pair, c.dt, grad_gamma, st));
         }
         if (grad_f)
             DCP_TRY(launch_ew(dtype, EW_SCALE, grad_f, nullptr, grad_f, c.gamma * c.dt, g.n,
-                              vec_ok_for(dtype, g, {grad_f}), st));
+                              ew_ok({grad_f}), st));
     }
     return DCP_OK;
 }
@@ -1066,12 +1081,11 @@ int dcp_revolve_forward(int dtype, void *u, const void *f, int64_t nx, int64_t n
     hipStream_t st = static_cast<hipStream_t>(stream);
     const RevBufs B{ws, &w, nslots, align_up(fb)};
     void *scratch = at(ws, w.scratch);
-    bool vok = vec_ok_for(dtype, g, {u, f, B.buf(kRvOrigin), B.buf(nslots), scratch});
-    for (int32_t i = 0; i < nslots; ++i) vok = vok && aligned16(B.buf(i));
-    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
+    const bool vok = vec_ok_for(dtype, g, {u, f, ws});
+    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
-    DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, B.buf(kRvOrigin), 0.0, g.n, vok, st));
+    DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, B.buf(kRvOrigin), 0.0, g.n, ew_ok({u, B.buf(kRvOrigin)}), st));
     // the schedule's opening chain of advances, u_0 -> ... -> u_{T-1}, stores
     // the snapshots the reverse sweep starts from
     int32_t last = kRvOrigin;
@@ -1119,9 +1133,9 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     if (T == 0 || g.n == 0) {
         if (g.n > 0)
             DCP_TRY(launch_ew(dtype, EW_COPY, lam_T, nullptr, grad_u0, 0.0, g.n,
-                              vec_ok_for(dtype, g, {lam_T, grad_u0}), st));
+                              ew_ok({lam_T, grad_u0}), st));
         if (grad_f && g.n > 0)
-            DCP_TRY(launch_ew(dtype, EW_ZERO, nullptr, nullptr, grad_f, 0.0, g.n, vec_ok_for(dtype, g, {grad_f}), st));
+            DCP_TRY(launch_ew(dtype, EW_ZERO, nullptr, nullptr, grad_f, 0.0, g.n, ew_ok({grad_f}), st));
         DCP_TRY(launch_zero(grad_ab, 2, st));
         if (grad_gamma) DCP_TRY(launch_zero(grad_gamma, 1, st));
         return DCP_OK;
@@ -1132,10 +1146,8 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     void *scratch = at(ws, w.scratch);
     void *lam[2] = {at(ws, w.lam), at(ws, w.lam + align_up(fb))};
     void *lsum = grad_f ? grad_f : (lsum_field ? static_cast<void *>(at(ws, w.lsum)) : nullptr);
-    bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, grad_f, B.buf(kRvOrigin), B.buf(nslots), scratch,
-                                     lam[0], lam[1], lsum});
-    for (int32_t i = 0; i < nslots; ++i) vok = vok && aligned16(B.buf(i));
-    const Tile t = pick_tile(dtype, g, vok, kRunBlocks);
+    const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, grad_f, ws});
+    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
@@ -1267,13 +1279,13 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
             double *dp = reinterpret_cast<double *>(at(ws, w.dot));
             const int nb = ew_norm_blocks(g.n);
             double *pair = dp + 2 * (size_t)nb;
-            DCP_TRY(launch_ew_dot(dtype, lsum, f, dp, g.n, vec_ok_for(dtype, g, {lsum, f}), st));
+            DCP_TRY(launch_ew_dot(dtype, lsum, f, dp, g.n, ew_ok({lsum, f}), st));
             DCP_TRY(launch_finalize(dp, nb, nb, 1, pair, nullptr, 0, st));
             DCP_TRY(launch_scalar_scale(pair, c.dt, grad_gamma, st));
         }
         if (grad_f)
             DCP_TRY(launch_ew(dtype, EW_SCALE, grad_f, nullptr, grad_f, c.gamma * c.dt, g.n,
-                              vec_ok_for(dtype, g, {grad_f}), st));
+                              ew_ok({grad_f}), st));
     }
     return DCP_OK;
 }

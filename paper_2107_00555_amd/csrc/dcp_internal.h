@@ -139,13 +139,17 @@ struct TbkArgs {
     int64_t nx, ny, nz;
     double c0, c1, c2;
     int ty, nslab, nseg, zc, wc, halo, chf;
-    int sblk;  // slabs per block of the tile order (see TbkTile)
+    int sblk;   // slabs per block of the tile order (see TbkTile)
+    int shift;  // points the last segment starts early (see TbkTile)
 };
 struct TbkTile {
     int B, vec, ty, nt, km;
     bool seg;             // x-segments with a halo (false: whole rows)
     int wc, halo, chf;    // segment chunks, halo chunks per side, frame chunks per row
     int nseg, nslab, zc, nruns, nblk;
+    // Ragged rows (nx not a whole number of chunks): the points the last
+    // segment starts early so that it ends with the row (0: whole chunks).
+    int shift;
     // Tile order within a z-run: blocks of sblk slabs, each block taking all
     // its segments (slab fastest), so that the tiles one XCD runs together
     // (a contiguous range) are neighbours along x and y.

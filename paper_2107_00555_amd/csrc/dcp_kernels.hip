@@ -40,9 +40,11 @@
 namespace dcp {
 namespace {
 
+// A lane's vector in global memory, aligned to its elements only (rows of any
+// length and views of any offset); the access is the same single instruction.
 template <typename T, int N>
 struct VecT {
-    typedef T type __attribute__((ext_vector_type(N)));
+    typedef T type __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
 template <typename T, int VEC>
@@ -138,8 +140,14 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
 
     const int64_t nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t sy = nx, sz = nx * ny;
-    const int64_t x0 = ((int64_t)tx * (64 * BXW) + wx * 64 + lane) * VEC;
-    const bool xok = x0 < nx;
+    const int64_t xt = ((int64_t)tx * (64 * BXW) + wx * 64 + lane) * VEC;
+    const bool xok = xt < nx;
+    // a row that is not a whole number of vectors (nx >= VEC, checked by the
+    // host): its last lane starts `sh` points earlier, so that it ends with the
+    // row; it and the lane before compute those points alike, and the sums
+    // take them from the lane before
+    const int sh = VEC > 1 && xok && xt + VEC > nx ? (int)(xt + VEC - nx) : 0;
+    const int64_t x0 = xt - sh;
     const int64_t yf = ((int64_t)ty * BY + wy) * RY;
     const int nrow = (int)max((int64_t)0, min((int64_t)RY, ny - yf));
     const bool active = xok && nrow > 0;
@@ -155,13 +163,17 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
 
     const int64_t ytop = wrap<BC>(yf - 1, ny);
     const int64_t ybot = wrap<BC>(yf + nrow, ny);
-    const bool need_l = xok && (lane == 0 || x0 == 0);
-    const bool need_r = xok && (lane == 63 || x0 + VEC >= nx);
+    // lanes whose neighbour is not the next lane's first or last point
+    const bool need_l = xok && (lane == 0 || x0 == 0 || sh);
+    const bool need_r = xok && (lane == 63 || xt + 2 * VEC > nx);
     const int64_t xl = wrap<BC>(x0 - 1, nx);
     const int64_t xr = wrap<BC>(x0 + VEC, nx);
 
     const T C0 = (T)a.c0, C1 = (T)a.c1, C2 = (T)a.c2;
     const T C1F = (T)a.c1f, C2F = (T)a.c2f;
+
+    // the value of element e in the sums: 0 where the lane before counts it
+    auto counts = [&](int e, T v) -> double { return e < VEC - 1 && e < sh ? 0.0 : (double)v; };
 
     // loaders for a resolved plane index zr (-1 = ghost plane) of a stencil
     // operand P (S, or V)
@@ -299,9 +311,9 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                                 acc = fma(-(C1 * c) * c, c, acc);
                                 res[e] = acc;
                                 if constexpr (RED) {
-                                    const double d = (double)acc;
+                                    const double d = counts(e, acc);
                                     acc0 = fma(d, d, acc0);
-                                    const double dd = d - (double)c;
+                                    const double dd = d - counts(e, c);
                                     acc1 = fma(dd, dd, acc1);
                                 }
                             } else {  // the adjoint ops: c = lambda_{t+1}, qv = u_t
@@ -310,8 +322,8 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                                 res[e] = acc;
                                 if constexpr (RED) {
                                     const double du = (double)qv;
-                                    acc0 = fma((double)lapn, du, acc0);
-                                    acc1 = fma((double)c, du * du * du, acc1);
+                                    acc0 = fma(counts(e, lapn), du, acc0);
+                                    acc1 = fma(counts(e, c), du * du * du, acc1);
                                 }
                             }
                         }
@@ -320,12 +332,18 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                     if constexpr (LSUM) {
                         // running sum of the adjoint inputs: lam += lambda_{t+1}
                         T *lp = static_cast<T *>(a.lam) + z * sz + (yf + r) * sy + x0;
-                        T lv[VEC];
-                        if (a.lam_first) zero_vec<T, VEC>(lv);
-                        else load_vec_nt<T, VEC>(lv, lp);
+                        if (sh) {  // the lane before adds to the first points
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) lv[e] = lv[e] + uc[r][e];
-                        store_vec_nt<T, VEC>(lp, lv);
+                            for (int e = 0; e < VEC; ++e)
+                                if (e >= sh) lp[e] = (a.lam_first ? T(0) : lp[e]) + uc[r][e];
+                        } else {
+                            T lv[VEC];
+                            if (a.lam_first) zero_vec<T, VEC>(lv);
+                            else load_vec_nt<T, VEC>(lv, lp);
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) lv[e] = lv[e] + uc[r][e];
+                            store_vec_nt<T, VEC>(lp, lv);
+                        }
                     }
                 }
             }

@@ -41,8 +41,12 @@ namespace {
 template <typename T, int N>
 struct KVec {
     typedef T type __attribute__((ext_vector_type(N)));
+    // in global memory a chunk is aligned to its elements only (rows of any
+    // length); the access is the same single instruction
+    typedef T gtype __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
+// 16-byte LDS accesses (16-byte aligned)
 template <typename T, int VEC>
 __device__ __forceinline__ void k_load(T (&d)[VEC], const T *p) {
     typedef typename KVec<T, VEC>::type V;
@@ -60,20 +64,28 @@ __device__ __forceinline__ void k_store(T *p, const T (&s)[VEC]) {
     *reinterpret_cast<V *>(p) = v;
 }
 
-// Streaming (non-temporal) forms for data a pass touches once: f and the
-// stored states.  u_t keeps ordinary loads: the neighbouring tiles read its
-// halo rows and chunks again through L2.
+// Global loads, and streaming (non-temporal) forms for data a pass touches
+// once.  u_t keeps ordinary loads: the neighbouring tiles read its halo rows
+// and chunks again through L2.
 template <typename T, int VEC>
-__device__ __forceinline__ void k_load_nt(T (&d)[VEC], const T *p) {
-    typedef typename KVec<T, VEC>::type V;
+__device__ __forceinline__ void k_gload(T (&d)[VEC], const T *p) {
+    typedef typename KVec<T, VEC>::gtype V;
+    V v = *reinterpret_cast<const V *>(p);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) d[i] = v[i];
+}
+
+template <typename T, int VEC>
+__device__ __forceinline__ void k_gload_nt(T (&d)[VEC], const T *p) {
+    typedef typename KVec<T, VEC>::gtype V;
     V v = __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
 #pragma unroll
     for (int i = 0; i < VEC; ++i) d[i] = v[i];
 }
 
 template <typename T, int VEC>
-__device__ __forceinline__ void k_store_nt(T *p, const T (&s)[VEC]) {
-    typedef typename KVec<T, VEC>::type V;
+__device__ __forceinline__ void k_gstore_nt(T *p, const T (&s)[VEC]) {
+    typedef typename KVec<T, VEC>::gtype V;
     V v;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) v[i] = s[i];
@@ -138,12 +150,13 @@ __device__ __forceinline__ T k_fwd(T c, T xm, T xp, T ym, T yp, T zm, T zp, T fq
 
 // Flag bits of a lane's chunk: bit 0 valid; bit s (1..B) the chunk's row
 // carries level s; bit 4 owned (a point of the tile, stored and reduced);
-// bit 5 ghost (Dirichlet: outside the grid, every level reads 0); the frame
+// bit 5 ghost (Dirichlet: outside the grid, every level reads 0); bit 6 the
+// chunk whose first points the segment before owns too (RAG); the frame
 // column from bit 8 up.
-constexpr unsigned kValid = 1u, kOwned = 16u, kGhost = 32u;
+constexpr unsigned kValid = 1u, kOwned = 16u, kGhost = 32u, kTwice = 64u;
 constexpr int kColShift = 8;
 
-template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RED>
+template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED>
 __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
     static_assert(B >= 2 && B <= 3, "two or three steps per pass");
     extern __shared__ __align__(16) unsigned char tbk_smem[];
@@ -152,7 +165,7 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
     const int TY = a.ty;
     const int CHF = a.chf;   // chunks per frame row
     const int FW = CHF * VEC;
-    const int CH = nx / VEC;  // chunks per grid row
+    const int CH = RAG ? (nx + VEC - 1) / VEC : nx / VEC;  // chunks per grid row
     const int R0 = TY + 2 * B;
     T *const L0 = reinterpret_cast<T *>(tbk_smem);
     // Plane buffer b of level s (1 .. B-1).  Level s lives on frame rows
@@ -180,8 +193,12 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
     const int y0 = slab * TY;
     const int z0 = zrun * a.zc;
     const int z1 = min(nz, z0 + a.zc);
-    const int gc0 = SEG ? seg * a.wc - a.halo : 0;  // grid chunk of frame column 0
-    const int oc0 = SEG ? a.halo : 0;               // owned frame columns [oc0, oc1)
+    // rows that are not whole chunks (RAG): the last segment starts `shift`
+    // points earlier, so that it ends with the row; those points belong to the
+    // segment before, and are computed by both
+    const int sh = RAG && seg == a.nseg - 1 ? a.shift : 0;
+    const int gx0 = SEG ? (seg * a.wc - a.halo) * VEC - sh : 0;  // grid column of frame column 0
+    const int oc0 = SEG ? a.halo : 0;                            // owned frame columns [oc0, oc1)
     const int oc1 = SEG ? a.halo + min(a.wc, CH - seg * a.wc) : CH;
 
     const T *__restrict__ U = static_cast<const T *>(a.u);
@@ -202,24 +219,30 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
         const int c = v ? idx % CHF : 0;
         const int gy = y0 - B + r;
         const int gyr = k_wrap<BC>(gy, ny);
-        const int gcr = SEG ? k_wrap<BC>(gc0 + c, CH) : c;
+        const int gxr = k_wrap<BC>(gx0 + c * VEC, nx);  // whole chunks are inside or outside the row
         lofs[k] = r * FW + c * VEC;
-        gofs[k] = (gyr >= 0 && gcr >= 0) ? gyr * nx + gcr * VEC : -1;
+        gofs[k] = (gyr >= 0 && gxr >= 0) ? gyr * nx + gxr : -1;
         unsigned fl = (v ? kValid : 0u) | ((unsigned)c << kColShift);
 #pragma unroll
         for (int s = 1; s <= B; ++s)
             if (v && r >= s && r < R0 - s) fl |= 1u << s;
         if (v && r >= B && r < B + TY && gy < ny && c >= oc0 && c < oc1) fl |= kOwned;
         if (gofs[k] < 0) fl |= kGhost;
+        if (RAG && sh && c == oc0) fl |= kTwice;
         flags[k] = fl;
     }
 
+    // a point's value in the norms: 0 where the segment before counts it
+    auto counts = [&](unsigned fl, int e, T v) -> double {
+        if constexpr (RAG) return (fl & kTwice) && e < sh ? 0.0 : (double)v;
+        return (double)v;
+    };
     auto load_u = [&](int zq, T (&d)[KM][VEC]) {
         const int zr = k_wrap<BC>(zq, nz);
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             if ((flags[k] & kValid) && gofs[k] >= 0 && zr >= 0)
-                k_load<T, VEC>(d[k], U + (int64_t)zr * sz + gofs[k]);
+                k_gload<T, VEC>(d[k], U + (int64_t)zr * sz + gofs[k]);
             else
                 k_zero<T, VEC>(d[k]);
         }
@@ -230,7 +253,7 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             if ((flags[k] & 2u) && gofs[k] >= 0 && zr >= 0)
-                k_load_nt<T, VEC>(d[k], F + (int64_t)zr * sz + gofs[k]);
+                k_gload_nt<T, VEC>(d[k], F + (int64_t)zr * sz + gofs[k]);
             else
                 k_zero<T, VEC>(d[k]);
         }
@@ -332,17 +355,17 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
                 const bool here = (fl & kOwned) && owned_plane;
                 if (s < B) {
                     k_store<T, VEC>(dst + o, res);
-                    if (mid && here) k_store_nt<T, VEC>(mid + (int64_t)p * sz + gofs[k], res);
+                    if (mid && here) k_gstore_nt<T, VEC>(mid + (int64_t)p * sz + gofs[k], res);
                 } else if (fl & kOwned) {
-                    k_store_nt<T, VEC>(O + (int64_t)p * sz + gofs[k], res);
+                    k_gstore_nt<T, VEC>(O + (int64_t)p * sz + gofs[k], res);
                 }
                 if constexpr (RED) {
                     if (here) {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
-                            const double d = (double)res[e];
+                            const double d = counts(fl, e, res[e]);
                             es[s - 1] = fma(d, d, es[s - 1]);
-                            const double dd = d - (double)c[e];
+                            const double dd = d - counts(fl, e, c[e]);
                             rs[s - 1] = fma(dd, dd, rs[s - 1]);
                         }
                     }
@@ -429,7 +452,7 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
 // Ring slots are (plane - q0) mod 3, compile-time constants in a plane loop
 // unrolled three times, so no register copies rotate the queues.  Every
 // point is computed with the one-step kernel's operations, as in tbk_kernel.
-template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RED>
+template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED>
 __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     static_assert(B >= 2 && B <= 3, "two or three steps per pass");
     extern __shared__ __align__(16) unsigned char tbk_smem[];
@@ -438,7 +461,7 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     const int TY = a.ty;
     const int CHF = a.chf;
     const int FW = CHF * VEC;
-    const int CH = nx / VEC;
+    const int CH = RAG ? (nx + VEC - 1) / VEC : nx / VEC;
     const int R0 = TY + 2 * B;
     T *const SM = reinterpret_cast<T *>(tbk_smem);
     // LDS: level 0 at planes of both parities (R0 rows each), then level s =
@@ -466,7 +489,8 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     const int y0 = slab * TY;
     const int z0 = zrun * a.zc;
     const int z1 = min(nz, z0 + a.zc);
-    const int gc0 = SEG ? seg * a.wc - a.halo : 0;
+    const int sh = RAG && seg == a.nseg - 1 ? a.shift : 0;  // as in tbk_kernel
+    const int gx0 = SEG ? (seg * a.wc - a.halo) * VEC - sh : 0;
     const int oc0 = SEG ? a.halo : 0;
     const int oc1 = SEG ? a.halo + min(a.wc, CH - seg * a.wc) : CH;
 
@@ -485,15 +509,16 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
         const int c = v ? idx % CHF : 0;
         const int gy = y0 - B + r;
         const int gyr = k_wrap<BC>(gy, ny);
-        const int gcr = SEG ? k_wrap<BC>(gc0 + c, CH) : c;
+        const int gxr = k_wrap<BC>(gx0 + c * VEC, nx);  // whole chunks are inside or outside the row
         lofs[k] = r * FW + c * VEC;
-        gofs[k] = (gyr >= 0 && gcr >= 0) ? gyr * nx + gcr * VEC : -1;
+        gofs[k] = (gyr >= 0 && gxr >= 0) ? gyr * nx + gxr : -1;
         unsigned fl = (v ? kValid : 0u) | ((unsigned)c << kColShift);
 #pragma unroll
         for (int s = 1; s <= B; ++s)
             if (v && r >= s && r < R0 - s) fl |= 1u << s;
         if (v && r >= B && r < B + TY && gy < ny && c >= oc0 && c < oc1) fl |= kOwned;
         if (gofs[k] < 0) fl |= kGhost;
+        if (RAG && sh && c == oc0) fl |= kTwice;
         flags[k] = fl;
     }
 
@@ -516,7 +541,7 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
         const int zr = k_wrap<BC>(zq, nz);
         const T *plane = U + (int64_t)(zr >= 0 ? zr : 0) * sz;
 #pragma unroll
-        for (int k = 0; k < KM; ++k) k_load<T, VEC>(d[k], at(plane, k));
+        for (int k = 0; k < KM; ++k) k_gload<T, VEC>(d[k], at(plane, k));
     };
     // f keeps ordinary loads here: the halo rows and columns of its frame are
     // read again by the neighbouring tiles (1.46 times the tile at 512^3 FP64),
@@ -526,7 +551,7 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
         const int zr = k_wrap<BC>(zq, nz);
         const T *plane = F + (int64_t)(zr >= 0 ? zr : 0) * sz;
 #pragma unroll
-        for (int k = 0; k < KM; ++k) k_load<T, VEC>(d[k], at(plane, k));
+        for (int k = 0; k < KM; ++k) k_gload<T, VEC>(d[k], at(plane, k));
     };
     // Dirichlet: level 0 at plane zq is zero on ghost chunks and planes
     auto ghost0 = [&](int zq, T (&d)[KM][VEC]) {
@@ -549,6 +574,12 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
         if (c < CHF - 1) rgt = wlane != 63 ? fu : base[o + VEC];
         else if (!SEG && BC == 1) rgt = base[o - c * VEC];
         else rgt = T(0);
+    };
+
+    // a point's value in the norms: 0 where the segment before counts it
+    auto counts = [&](unsigned fl, int e, T v) -> double {
+        if constexpr (RAG) return (fl & kTwice) && e < sh ? 0.0 : (double)v;
+        return (double)v;
     };
 
     // rings: slot (plane - q0) mod 3
@@ -634,17 +665,17 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
                 if (s < B) {
                     k_store<T, VEC>(dst + o, res);
                     k_copy<T, VEC>(Lo[k], res);
-                    if (mid && here) k_store_nt<T, VEC>(const_cast<T *>(at(mid + (int64_t)p * sz, k)), res);
+                    if (mid && here) k_gstore_nt<T, VEC>(const_cast<T *>(at(mid + (int64_t)p * sz, k)), res);
                 } else if (fl & kOwned) {
-                    k_store_nt<T, VEC>(const_cast<T *>(at(O + (int64_t)p * sz, k)), res);
+                    k_gstore_nt<T, VEC>(const_cast<T *>(at(O + (int64_t)p * sz, k)), res);
                 }
                 if constexpr (RED) {
                     if (here) {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
-                            const double d = (double)res[e];
+                            const double d = counts(fl, e, res[e]);
                             es[s - 1] = fma(d, d, es[s - 1]);
-                            const double dd = d - (double)Lc[k][e];
+                            const double dd = d - counts(fl, e, Lc[k][e]);
                             rs[s - 1] = fma(dd, dd, rs[s - 1]);
                         }
                     }
@@ -719,35 +750,43 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     }
 }
 
-template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RED, bool RING>
+template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED, bool RING>
 auto tbk_fn() {
-    if constexpr (RING) return tbr_kernel<T, VEC, B, NT, KM, BC, SEG, RED>;
-    else return tbk_kernel<T, VEC, B, NT, KM, BC, SEG, RED>;
+    if constexpr (RING) return tbr_kernel<T, VEC, B, NT, KM, BC, SEG, RAG, RED>;
+    else return tbk_kernel<T, VEC, B, NT, KM, BC, SEG, RAG, RED>;
 }
 
 template <typename T, int VEC, int B, int NT, int KM, bool RING>
 hipError_t tbk_launch_t(int bc, bool reduce, const TbkTile &t, const TbkArgs &a, hipStream_t st) {
     const dim3 grid(t.nblk), block(NT);
     const size_t lds = t.lds_bytes;
-#define DCP_TBK(BCV, SEGV, REDV)                                                                     \
+#define DCP_TBK(BCV, SEGV, RAGV, REDV)                                                               \
     do {                                                                                             \
-        auto fn = tbk_fn<T, VEC, B, NT, KM, BCV, SEGV, REDV, RING>();                                \
+        auto fn = tbk_fn<T, VEC, B, NT, KM, BCV, SEGV, RAGV, REDV, RING>();                          \
         hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),                      \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);   \
         if (e_ != hipSuccess) return e_;                                                             \
         hipLaunchKernelGGL(fn, grid, block, lds, st, a);                                             \
     } while (0)
-#define DCP_TBK_RED(BCV, SEGV)             \
-    do {                                   \
-        if (reduce) DCP_TBK(BCV, SEGV, true); \
-        else DCP_TBK(BCV, SEGV, false);    \
+#define DCP_TBK_RED(BCV, SEGV, RAGV)                \
+    do {                                            \
+        if (reduce) DCP_TBK(BCV, SEGV, RAGV, true); \
+        else DCP_TBK(BCV, SEGV, RAGV, false);       \
     } while (0)
-    if (bc == 0) {
-        if (t.seg) DCP_TBK_RED(0, true);
-        else DCP_TBK_RED(0, false);
+    if (t.shift) {
+        // the planner gives ragged rows these two forms only
+        if constexpr ((RING && B == 3) || (NT == 1024 && B == 2)) {
+            if (bc == 0) DCP_TBK_RED(0, true, true);
+            else DCP_TBK_RED(1, true, true);
+        } else {
+            return hipErrorInvalidValue;
+        }
+    } else if (bc == 0) {
+        if (t.seg) DCP_TBK_RED(0, true, false);
+        else DCP_TBK_RED(0, false, false);
     } else {
-        if (t.seg) DCP_TBK_RED(1, true);
-        else DCP_TBK_RED(1, false);
+        if (t.seg) DCP_TBK_RED(1, true, false);
+        else DCP_TBK_RED(1, false, false);
     }
 #undef DCP_TBK_RED
 #undef DCP_TBK
@@ -782,73 +821,92 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
     const int esz = dtype == 0 ? 8 : 4;
     const int vec = 16 / esz;
     if (B < 2 || B > 3) return false;
-    if (!vec_ok || nx <= 0 || ny <= 0 || nz <= 0 || nx % vec != 0) return false;
+    if (!vec_ok || nx <= 0 || ny <= 0 || nz <= 0) return false;
     if (nx > (1 << 24) || nx * ny > (int64_t)INT32_MAX || nz > (1 << 29) || ny > (1 << 29)) return false;
-    const int64_t ch = nx / vec;
+    const int64_t ch = (nx + vec - 1) / vec;
+    const int shift = (int)(ch * vec - nx);
     const int halo = (B + vec - 1) / vec;
     const TbkLanes ln = kTbkLanes[lanes == 512 ? 1 : lanes == 768 ? 2 : 0];
+    // ragged rows: the three-step ring form and the two-step plain form only
+    if (shift && !(B == 3 ? ln.ring : ln.nt == 1024)) return false;
     // the ring form addresses a chunk as a plane base plus a 32-bit offset
     // (the tile limits below already keep its planes under 1 GiB)
     if (ln.ring && nx * ny * esz > (int64_t)UINT32_MAX) return false;
-    // Candidates: whole rows, or segments of 256, 128, 64 or 32 chunks; slabs
-    // of 16, 8 or 4 rows.  Each must fit the lanes and the LDS; the planner
-    // takes the one that recomputes the fewest points per owned point (the
-    // halo rows and chunks of levels 1 .. B-1), whole rows first on a tie.
-    double best = 1e30;
+    double best = 1e300;
     bool found = false;
-    const int64_t widths[] = {ch, 256, 128, 64, 32};
-    for (int64_t wc : widths) {
-        if (wc > ch) continue;
+    auto consider = [&](int64_t wc, int ty) {
         const bool seg = wc < ch;
-        if (force_wc > 0 && (seg ? wc != force_wc : force_wc < ch)) continue;
+        const int64_t nseg = (ch + wc - 1) / wc;
+        // a chunk of a ragged row lies inside it whole: at least two segments,
+        // the last one wider than the halo
+        if (shift && (!seg || ch - (nseg - 1) * wc < halo + 1 || wc < halo + 1)) return;
         const int64_t chf = seg ? wc + 2 * halo : ch;
-        for (int ty : {16, 8, 4}) {
-            if (force_ty > 0 && ty != force_ty) continue;
-            const int r0 = ty + 2 * B;
-            if ((int64_t)r0 * chf > (int64_t)ln.nt * ln.km) continue;
-            const size_t lds = (size_t)tbk_lds_rows(B, ty, ln.ring) * (size_t)chf * 16;
-            if (lds > lds_limit) continue;
-            if (lds < (size_t)(ln.nt / 64) * 2 * B * sizeof(double)) continue;
-            const int64_t nslab = (ny + ty - 1) / ty;
-            const int64_t nseg = (ch + wc - 1) / wc;
-            if (nslab * nseg > 65536) continue;
-            double work = 0.0;
-            for (int s = 1; s <= B; ++s) work += (double)(ty + 2 * (B - s)) * (double)chf;
-            const double cost = work / ((double)ty * (double)wc * B);
-            if (cost < best - 1e-9) {
-                best = cost;
-                found = true;
-                int64_t cols = nslab * nseg;
-                int64_t runs = 256 / cols;
-                if (runs < 1) runs = 1;
-                if (runs > nz) runs = nz;
-                int64_t zc = (nz + runs - 1) / runs;
-                runs = (nz + zc - 1) / zc;
-                t->B = B;
-                t->vec = vec;
-                t->ty = ty;
-                t->nt = ln.nt;
-                t->km = ln.km;
-                t->seg = seg;
-                t->wc = (int)wc;
-                t->halo = seg ? halo : 0;
-                t->chf = (int)chf;
-                t->nseg = (int)nseg;
-                t->nslab = (int)nslab;
-                t->zc = (int)zc;
-                t->nruns = (int)runs;
-                t->nblk = (int)(cols * runs);
-                t->lds_bytes = lds;
-                // the 256 workgroups go round-robin to the 8 XCDs and are
-                // renumbered so each XCD holds a contiguous run of tiles:
-                // make that run a block of slabs across all segments, so the
-                // halo rows and chunks a tile shares with its neighbours are
-                // read through the same L2 (measured at 512^3 FP64: reads per
-                // pass 2.55 -> 2.28 GiB, 1.14x the algorithmic 2 GiB)
-                int64_t per = (t->nblk + 7) / 8 / nseg;
-                t->sblk = (int)(per < 1 ? 1 : per > nslab ? nslab : per);
-            }
+        const int r0 = ty + 2 * B;
+        if ((int64_t)r0 * chf > (int64_t)ln.nt * ln.km) return;
+        const size_t lds = (size_t)tbk_lds_rows(B, ty, ln.ring) * (size_t)chf * 16;
+        if (lds > lds_limit) return;
+        if (lds < (size_t)(ln.nt / 64) * 2 * B * sizeof(double)) return;
+        const int64_t nslab = (ny + ty - 1) / ty;
+        if (nslab * nseg > 65536) return;
+        const int64_t cols = nslab * nseg;
+        int64_t runs = 256 / cols;
+        if (runs < 1) runs = 1;
+        if (runs > nz) runs = nz;
+        const int64_t zc = (nz + runs - 1) / runs;
+        runs = (nz + zc - 1) / zc;
+        // time of a pass: rounds of 256 workgroups, planes of a z-run with the
+        // 2(B-1) that fill and drain its pipeline and about three for the
+        // prologue, and a plane's time, about half of which depends on the
+        // frame's size
+        const double plane = 1.0 + (double)(r0 * chf) / (double)(ln.nt * ln.km);
+        const double cost = (double)((cols * runs + 255) / 256) * (double)(zc + 2 * (B - 1) + 3) * plane;
+        if (cost >= best * (1 - 1e-9)) return;
+        best = cost;
+        found = true;
+        t->B = B;
+        t->vec = vec;
+        t->ty = ty;
+        t->nt = ln.nt;
+        t->km = ln.km;
+        t->seg = seg;
+        t->shift = shift;
+        t->wc = (int)wc;
+        t->halo = seg ? halo : 0;
+        t->chf = (int)chf;
+        t->nseg = (int)nseg;
+        t->nslab = (int)nslab;
+        t->zc = (int)zc;
+        t->nruns = (int)runs;
+        t->nblk = (int)(cols * runs);
+        t->lds_bytes = lds;
+        // the 256 workgroups go round-robin to the 8 XCDs and are
+        // renumbered so each XCD holds a contiguous run of tiles:
+        // make that run a block of slabs across all segments, so the
+        // halo rows and chunks a tile shares with its neighbours are
+        // read through the same L2 (measured at 512^3 FP64: reads per
+        // pass 2.55 -> 2.28 GiB, 1.14x the algorithmic 2 GiB)
+        const int64_t per = (t->nblk + 7) / 8 / nseg;
+        t->sblk = (int)(per < 1 ? 1 : per > nslab ? nslab : per);
+    };
+    if (force_wc > 0 || force_ty > 0) {
+        const int64_t widths[] = {ch, 256, 128, 64, 32};
+        for (int64_t wc : widths) {
+            if (wc > ch || (force_wc > 0 && (wc < ch ? wc != force_wc : force_wc < ch))) continue;
+            for (int ty : {16, 8, 4})
+                if (force_ty <= 0 || ty == force_ty) consider(wc, ty);
         }
+        return found;
+    }
+    // Rows whole or cut into even segments of at least 8 chunks (ragged rows:
+    // 4), slabs of 2 to 24 rows.  Measured against the choice among 16, 8 and 4
+    // rows and segments of 256, 128, 64 and 32 chunks that recomputes the
+    // fewest points, three steps per pass, us per step: FP64 160^3 16.1 -> 11.7,
+    // 192^3 20.7 -> 16.6, 256^3 34.3 -> 30.4, 320^3 66.8 -> 55.2, 1030 x 515 x
+    // 200 298 -> 175, 512^3 the same tiles; FP32 320^3 46.7 -> 33.3.
+    for (int64_t nseg = 1; nseg <= ch; ++nseg) {
+        const int64_t wc = (ch + nseg - 1) / nseg;
+        if (nseg > 1 && wc < (shift ? 4 : 8)) break;
+        for (int ty = 24; ty >= 2; --ty) consider(wc, ty);
     }
     return found;
 }

@@ -38,6 +38,8 @@ namespace {
 template <typename T, int N>
 struct TbVec {
     typedef T type __attribute__((ext_vector_type(N)));
+    // global memory: aligned to the elements only (rows of any length)
+    typedef T gtype __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
 template <typename T, int VEC>
@@ -65,6 +67,15 @@ __device__ __forceinline__ void tb_store(T *p, const T (&s)[VEC]) {
     }
 }
 
+// Global forms; tb_load and tb_store above are for LDS (16-byte aligned).
+template <typename T, int VEC>
+__device__ __forceinline__ void tb_gload(T (&d)[VEC], const T *p) {
+    typedef typename TbVec<T, VEC>::gtype V;
+    V v = *reinterpret_cast<const V *>(p);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) d[i] = v[i];
+}
+
 // Streaming (non-temporal) forms for data a pass touches once: the point
 // operands, the stored states and the running sum.  The stencil operand
 // keeps ordinary loads: neighbouring slabs read its halo rows again
@@ -74,7 +85,7 @@ __device__ __forceinline__ void tb_load_nt(T (&d)[VEC], const T *p) {
     if constexpr (VEC == 1) {
         d[0] = __builtin_nontemporal_load(p);
     } else {
-        typedef typename TbVec<T, VEC>::type V;
+        typedef typename TbVec<T, VEC>::gtype V;
         V v = __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
 #pragma unroll
         for (int i = 0; i < VEC; ++i) d[i] = v[i];
@@ -86,7 +97,7 @@ __device__ __forceinline__ void tb_store_nt(T *p, const T (&s)[VEC]) {
     if constexpr (VEC == 1) {
         __builtin_nontemporal_store(s[0], p);
     } else {
-        typedef typename TbVec<T, VEC>::type V;
+        typedef typename TbVec<T, VEC>::gtype V;
         V v;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) v[i] = s[i];
@@ -174,7 +185,12 @@ __device__ __forceinline__ T tb_adj(T c, T xm, T xp, T ym, T yp, T zm, T zp, T u
 //   norms of steps t+1 and t+2; MID also stores u_{t+1} on the owned points.
 // OP = SOP_ADJ: level 0 = lambda_{t+1}, point operands u_t (level 1) and
 //   u_{t-1} (level 2), sums = the parameter sums of steps t and t-1.
-template <typename T, int VEC, int TY, int NT, int KM, int BC, int OP, bool RED, bool MID>
+// RAG: rows that are not whole chunks.  The last chunk of a row starts `sh`
+// points early, so that it ends with the row; it computes those points too,
+// and the chunk before counts them.  In LDS a row keeps whole chunks, the last
+// one right behind its neighbour, so only the x-neighbours of these two chunks
+// lie elsewhere (y and z neighbours sit in the same place of their row).
+template <typename T, int VEC, int TY, int NT, int KM, int BC, int OP, bool RED, bool MID, bool RAG>
 __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
     constexpr int kTbThreads = NT;
     constexpr int kTbKmax = KM;
@@ -185,12 +201,14 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
     constexpr int R1 = TY + 2;  // level-1 rows: global rows y0-1 .. y0+TY
     const int nx = (int)a.nx, ny = (int)a.ny, nz = (int)a.nz;
     const int64_t sz = a.nx * a.ny;
-    const int CH = nx / VEC;
+    const int CH = RAG ? (nx + VEC - 1) / VEC : nx / VEC;
+    const int FW = RAG ? CH * VEC : nx;  // LDS row
+    const int sh = RAG ? FW - nx : 0;
     T *L0 = reinterpret_cast<T *>(tb_smem);
     // level-1 buffer b (0 or 1) starts R0 + b*R1 rows into the LDS area; an
     // offset from L0 (not a pointer picked from an array) keeps every access
     // an LDS instruction
-    auto L1 = [&](int b) -> T * { return L0 + (R0 + (b & 1) * R1) * nx; };
+    auto L1 = [&](int b) -> T * { return L0 + (R0 + (b & 1) * R1) * FW; };
 
     const int tid = threadIdx.x;
     const int L = tb_xcd_remap(blockIdx.x, gridDim.x);
@@ -208,7 +226,7 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
     const T C0 = (T)a.c0, C1 = (T)a.c1, C2 = (T)a.c2;
 
     // The lane's points: chunk k covers level-0 frame row r = idx / CH and
-    // x = (idx % CH) * VEC.  lofs = r*nx + x (LDS offset in the level-0 frame,
+    // x = (idx % CH) * VEC.  lofs = r*FW + x (LDS offset in the level-0 frame,
     // the level-1 buffers use the same frame shifted down one row), gofs = the
     // global offset of (x, row) in a plane, or -1 for a ghost row.
     int lofs[kTbKmax];
@@ -222,8 +240,8 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
         const int xo = v ? (idx % CH) * VEC : 0;
         const int gy = y0 - 2 + r;
         const int gyr = tb_wrap<BC>(gy, ny);
-        lofs[k] = r * nx + xo;
-        gofs[k] = gyr >= 0 ? gyr * nx + xo : -1;
+        lofs[k] = r * FW + xo;
+        gofs[k] = gyr >= 0 ? gyr * nx + (RAG && xo + VEC == FW ? xo - sh : xo) : -1;
         flags[k] = (v ? 1u : 0u) | ((v && r >= 1 && r <= TY + 2) ? 2u : 0u) |
                    ((v && r >= 2 && r <= TY + 1 && gy < ny) ? 4u : 0u) | ((unsigned)xo << 3);
     }
@@ -233,7 +251,7 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
 #pragma unroll
         for (int k = 0; k < kTbKmax; ++k) {
             if ((flags[k] & 1u) && gofs[k] >= 0 && zr >= 0)
-                tb_load<T, VEC>(d[k], U + (int64_t)zr * sz + gofs[k]);
+                tb_gload<T, VEC>(d[k], U + (int64_t)zr * sz + gofs[k]);
             else
                 tb_zero<T, VEC>(d[k]);
         }
@@ -260,15 +278,17 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
     };
     // x-neighbours of the chunk at LDS offset o (row start o - xo)
     auto xleft = [&](const T *base, int o, int xo) -> T {
-        if (xo > 0) return base[o - 1];
-        if constexpr (BC == 1) return base[o - xo + nx - 1];
+        if (xo > 0) return base[RAG && xo + VEC == FW ? o - 1 - sh : o - 1];
+        if constexpr (BC == 1) return base[o - xo + FW - 1];
         return T(0);
     };
     auto xright = [&](const T *base, int o, int xo) -> T {
-        if (xo + VEC < nx) return base[o + VEC];
+        if (xo + VEC < FW) return base[RAG && xo + 2 * VEC == FW ? o + VEC + sh : o + VEC];
         if constexpr (BC == 1) return base[o - xo];
         return T(0);
     };
+    // sums: whether element e of the chunk counts, and the running sum's points
+    auto twice = [&](int xo, int e) -> bool { return RAG && xo + VEC == FW && e < sh; };
     // The neighbouring chunks of a row are held by the neighbouring lanes
     // (chunk idx - 1 by lane - 1, idx + 1 by lane + 1, in the same stage), so
     // the x-neighbours come across the wave; the first and last lane of a
@@ -277,8 +297,8 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
     auto xnbrs = [&](const T *base, int o, int xo, const T (&c)[VEC], T &lft, T &rgt) {
         const T fl = tb_dpp<0x138>(c[VEC - 1]);
         const T fu = tb_dpp<0x130>(c[0]);
-        lft = (wlane != 0 && xo > 0) ? fl : xleft(base, o, xo);
-        rgt = (wlane != 63 && xo + VEC < nx) ? fu : xright(base, o, xo);
+        lft = (wlane != 0 && xo > 0 && !(RAG && xo + VEC == FW)) ? fl : xleft(base, o, xo);
+        rgt = (wlane != 63 && xo + VEC < FW && !(RAG && xo + 2 * VEC == FW)) ? fu : xright(base, o, xo);
     };
 
     // register queues: level 0 at q-1, q+1 and the prefetched q+2; level 1 at
@@ -336,8 +356,8 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
                 tb_zero<T, VEC>(bn[k]);
             } else {
                 T ym[VEC], yp[VEC];
-                tb_load<T, VEC>(ym, L0 + o - nx);
-                tb_load<T, VEC>(yp, L0 + o + nx);
+                tb_load<T, VEC>(ym, L0 + o - FW);
+                tb_load<T, VEC>(yp, L0 + o + FW);
                 T lft, rgt;
                 xnbrs(L0, o, xo, c, lft, rgt);
 #pragma unroll
@@ -346,14 +366,14 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
                     const T xp = e == VEC - 1 ? rgt : c[e + 1 < VEC ? e + 1 : e];
                     if constexpr (ADJ) {
                         bn[k][e] = tb_adj<T>(c[e], xm, xp, ym[e], yp[e], am[k][e], ap[k][e], qac[k][e], C0, C1,
-                                             sum_here, e1, r1);
+                                             sum_here && !twice(xo, e), e1, r1);
                     } else {
                         bn[k][e] = tb_fwd<T>(c[e], xm, xp, ym[e], yp[e], am[k][e], ap[k][e], qac[k][e], C0, C1,
                                              C2);
                     }
                 }
             }
-            tb_store<T, VEC>(L1w + o - nx, bn[k]);
+            tb_store<T, VEC>(L1w + o - FW, bn[k]);
             if constexpr (MID)
                 if (sum_here) tb_store_nt<T, VEC>(M + (int64_t)q * sz + gofs[k], bn[k]);
             if constexpr (RED && !ADJ) {
@@ -375,12 +395,12 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
 #pragma unroll
             for (int k = 0; k < kTbKmax; ++k) {
                 if (!(flags[k] & 4u)) continue;
-                const int o = lofs[k] - nx;  // level-1 buffer offset
+                const int o = lofs[k] - FW;  // level-1 buffer offset
                 const int xo = (int)(flags[k] >> 3);
                 T c[VEC], ym[VEC], yp[VEC], res[VEC];
                 tb_load<T, VEC>(c, L1r + o);
-                tb_load<T, VEC>(ym, L1r + o - nx);
-                tb_load<T, VEC>(yp, L1r + o + nx);
+                tb_load<T, VEC>(ym, L1r + o - FW);
+                tb_load<T, VEC>(yp, L1r + o + FW);
                 T lft, rgt;
                 xnbrs(L1r, o, xo, c, lft, rgt);
 #pragma unroll
@@ -389,7 +409,7 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
                     const T xp = e == VEC - 1 ? rgt : c[e + 1 < VEC ? e + 1 : e];
                     if constexpr (ADJ) {
                         res[e] = tb_adj<T>(c[e], xm, xp, ym[e], yp[e], bm[k][e], bn[k][e], qbm[k][e], C0, C1,
-                                           true, e2, r2);
+                                           !twice(xo, e), e2, r2);
                     } else {
                         res[e] = tb_fwd<T>(c[e], xm, xp, ym[e], yp[e], bm[k][e], bn[k][e], qbm[k][e], C0, C1,
                                            C2);
@@ -400,12 +420,18 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
                     // running sum of the adjoint inputs, in step order:
                     // lam = (lam + lambda_{t+1}) + lambda_t (level 0 at q-1 is in am)
                     T *lp = static_cast<T *>(a.lam) + (int64_t)(q - 1) * sz + gofs[k];
-                    T lv[VEC];
-                    if (a.lam_first) tb_zero<T, VEC>(lv);
-                    else tb_load_nt<T, VEC>(lv, lp);
+                    if (RAG && xo + VEC == FW) {  // the chunk before adds to the first points
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) lv[e] = (lv[e] + am[k][e]) + c[e];
-                    tb_store_nt<T, VEC>(lp, lv);
+                        for (int e = 0; e < VEC; ++e)
+                            if (e >= sh) lp[e] = ((a.lam_first ? T(0) : lp[e]) + am[k][e]) + c[e];
+                    } else {
+                        T lv[VEC];
+                        if (a.lam_first) tb_zero<T, VEC>(lv);
+                        else tb_load_nt<T, VEC>(lv, lp);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) lv[e] = (lv[e] + am[k][e]) + c[e];
+                        tb_store_nt<T, VEC>(lp, lv);
+                    }
                 }
                 if constexpr (RED && !ADJ) {
 #pragma unroll
@@ -424,7 +450,7 @@ __global__ void __launch_bounds__(NT) tb2_kernel(TbArgs a) {
 #pragma unroll
         for (int k = 0; k < kTbKmax; ++k) {
             if (flags[k] & 1u) tb_load<T, VEC>(am[k], L0 + lofs[k]);
-            if (flags[k] & 2u) tb_load<T, VEC>(bm[k], L1(q - 1) + lofs[k] - nx);
+            if (flags[k] & 2u) tb_load<T, VEC>(bm[k], L1(q - 1) + lofs[k] - FW);
         }
         __syncthreads();
 #pragma unroll
@@ -473,34 +499,42 @@ hipError_t tb_launch_t(int op, int bc, bool reduce, bool mid, const TbTile &t, c
                        hipStream_t st) {
     const dim3 grid(t.nblk), block(NT);
     const size_t lds = t.lds_bytes;
-#define DCP_TB(BCV, OPV, REDV, MIDV)                                                                  \
+#define DCP_TB(BCV, OPV, REDV, MIDV, RAGV)                                                            \
     do {                                                                                              \
-        auto fn = tb2_kernel<T, VEC, TY, NT, KM, BCV, OPV, REDV, MIDV>;                               \
+        auto fn = tb2_kernel<T, VEC, TY, NT, KM, BCV, OPV, REDV, MIDV, RAGV>;                         \
         hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),                       \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
         if (e_ != hipSuccess) return e_;                                                              \
         hipLaunchKernelGGL(fn, grid, block, lds, st, a);                                              \
     } while (0)
-    if (op == SOP_ADJ) {
-        if (bc == 0) DCP_TB(0, SOP_ADJ, true, false);
-        else DCP_TB(1, SOP_ADJ, true, false);
+    const bool rag = a.nx % VEC != 0;  // adjoint passes only (the forward ones take x-segments)
+    if (rag && op == SOP_FWD) return hipErrorInvalidValue;
+    if (op == SOP_ADJ && rag) {
+        if (bc == 0) DCP_TB(0, SOP_ADJ, true, false, true);
+        else DCP_TB(1, SOP_ADJ, true, false, true);
+    } else if (op == SOP_ADJ) {
+        if (bc == 0) DCP_TB(0, SOP_ADJ, true, false, false);
+        else DCP_TB(1, SOP_ADJ, true, false, false);
+    } else if (op == SOP_ADJL && rag) {
+        if (bc == 0) DCP_TB(0, SOP_ADJL, true, false, true);
+        else DCP_TB(1, SOP_ADJL, true, false, true);
     } else if (op == SOP_ADJL) {
-        if (bc == 0) DCP_TB(0, SOP_ADJL, true, false);
-        else DCP_TB(1, SOP_ADJL, true, false);
+        if (bc == 0) DCP_TB(0, SOP_ADJL, true, false, false);
+        else DCP_TB(1, SOP_ADJL, true, false, false);
     } else if (mid) {
         if (bc == 0) {
-            if (reduce) DCP_TB(0, SOP_FWD, true, true);
-            else DCP_TB(0, SOP_FWD, false, true);
+            if (reduce) DCP_TB(0, SOP_FWD, true, true, false);
+            else DCP_TB(0, SOP_FWD, false, true, false);
         } else {
-            if (reduce) DCP_TB(1, SOP_FWD, true, true);
-            else DCP_TB(1, SOP_FWD, false, true);
+            if (reduce) DCP_TB(1, SOP_FWD, true, true, false);
+            else DCP_TB(1, SOP_FWD, false, true, false);
         }
     } else if (bc == 0) {
-        if (reduce) DCP_TB(0, SOP_FWD, true, false);
-        else DCP_TB(0, SOP_FWD, false, false);
+        if (reduce) DCP_TB(0, SOP_FWD, true, false, false);
+        else DCP_TB(0, SOP_FWD, false, false, false);
     } else {
-        if (reduce) DCP_TB(1, SOP_FWD, true, false);
-        else DCP_TB(1, SOP_FWD, false, false);
+        if (reduce) DCP_TB(1, SOP_FWD, true, false, false);
+        else DCP_TB(1, SOP_FWD, false, false, false);
     }
 #undef DCP_TB
     return hipGetLastError();
@@ -526,15 +560,15 @@ constexpr int kNumTbCfgs = sizeof(kTbCfgs) / sizeof(kTbCfgs[0]);
 bool tb_plan(int dtype, int64_t nx, int64_t ny, int64_t nz, bool vec_ok, size_t lds_limit, TbTile *t) {
     const int esz = dtype == 0 ? 8 : 4;
     const int vec = 16 / esz;
-    if (!vec_ok || nx <= 0 || ny <= 0 || nz <= 0 || nx % vec != 0) return false;
+    if (!vec_ok || nx < vec || ny <= 0 || nz <= 0) return false;
     if (nx > (1 << 24) || nx * ny > (int64_t)INT32_MAX || nz > (1 << 29) || ny > (1 << 29)) return false;
-    const int64_t ch = nx / vec;
+    const int64_t ch = (nx + vec - 1) / vec;
     const char *forced = tuning_env("DCP_TB_CFG");  // tuning runs only
     const int only = (forced && *forced) ? std::atoi(forced) : -1;
     for (int i = 0; i < kNumTbCfgs; ++i) {
         if (only >= 0 && i != only) continue;
         const TbCfg c = kTbCfgs[i];
-        const size_t lds = (size_t)((c.ty + 4) + 2 * (c.ty + 2)) * (size_t)nx * esz;
+        const size_t lds = (size_t)((c.ty + 4) + 2 * (c.ty + 2)) * (size_t)ch * 16;
         if ((c.ty + 4) * ch > (int64_t)c.km * c.nt) continue;
         if (lds > lds_limit) continue;
         if (lds < (size_t)(c.nt / 64) * 4 * sizeof(double)) continue;
