@@ -90,8 +90,8 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
 }
 
 // Tile of the one-step kernels.  Two rows per lane (shape 1) and short z-runs:
-// 8 planes, fewer where that leaves under 2048 workgroups, down to 2, and to 1
-// under 512; the planes a run shares with the next come from the XCD's L2,
+// 8 planes, fewer where that leaves under 1200 workgroups (FP32: 900), down
+// to 2, and to 1 under 512; the planes a run shares with the next come from the XCD's L2,
 // and the many short workgroups keep every CU busy to the end.  Measured, us
 // per step with norms, against four rows per lane with runs of 8 to 64
 // planes: FP64 64^3 4.9 / 12.2, 96^3 7.8 / 14.1, 128^3 12.8 / 17.9, 192^3
@@ -113,7 +113,7 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
             return nb < 0 ? INT32_MAX : nb;
         };
         zc = 8;
-        while (zc > 2 && blocks(zc) < 2048) zc /= 2;
+        while (zc > 2 && blocks(zc) < (dtype == DCP_F64 ? 1200 : 900)) zc /= 2;
         if (zc == 2 && blocks(2) < 512) zc = 1;
         if (!forced && blocks(zc) > most) shape = 0;
         while (zc < 64 && blocks(zc) > most) zc *= 2;
@@ -203,6 +203,14 @@ bool tbk_for(int dtype, const Geo &g, int B, bool vok, size_t lds_limit, TbkTile
     return true;
 }
 
+// Plan of a B-step pass over blocks (dcp_block.hip), the first choice on small
+// grids; off while a tuning override forces one of the marching forms.
+bool blk_for(int dtype, const Geo &g, int B, size_t lds_limit, BlkTile *t) {
+    for (const char *name : {"DCP_TB_CFG", "DCP_TBK_CFG"})
+        if (const char *e = tuning_env(name); e && *e) return false;
+    return blk_plan(dtype, B, g.nx, g.ny, g.nz, lds_limit, t);
+}
+
 int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, bool norms, RunWs *w) {
     size_t off = 0;
     if (g.n == 0 || T == 0) {
@@ -225,6 +233,8 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
         for (int B = 2; impl == DCP_FUSED && B <= tblock && B <= 3; ++B) {
             TbkTile tk;
             if (tbk_for(dtype, g, B, true, kLdsMax, &tk) && tk.nblk > nb) nb = tk.nblk;
+            BlkTile bk;
+            if (blk_for(dtype, g, B, kLdsMax, &bk) && bk.nblk > nb) nb = bk.nblk;
         }
         w->nblk = nb;
         w->partials = off;
@@ -257,6 +267,8 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) && tb.nblk > nb) nb = tb.nblk;
+        BlkTile bk;
+        if (tblock >= 2 && blk_for(dtype, g, 2, kLdsMax, &bk) && bk.nblk > nb) nb = bk.nblk;
         w->nblk = nb;
         w->lam = off;
         off += 2 * align_up(g.bytes());
@@ -404,16 +416,19 @@ constexpr int64_t kRaggedMin = (int64_t)1 << 18;
 // The passes of a fused dcp_run: three steps where tblock >= 3 and the
 // B-step kernel applies; two steps over whole rows where the two-step kernel
 // applies, else over x-segments; one step otherwise and for the remainders.
+// Small grids take two and three steps over blocks.
 // stride: partial-sum slots per step of the run's workspace (norms only).
 struct PassPlan {
     bool use_tb = false, use_k2 = false, use_k3 = false;
+    bool use_b2 = false, use_b3 = false;  // over blocks, before the others
     TbTile tb{};
     TbkTile k2{}, k3{};
+    BlkTile b2{}, b3{};
     // steps in the pass starting at step s of T: three where possible, but
     // four steps left go as two passes of two (cheaper than three and one)
     int32_t len_at(int32_t s, int32_t T) const {
-        const bool two = use_tb || use_k2;
-        if (use_k3 && s + 3 <= T && !(two && T - s == 4)) return 3;
+        const bool two = use_tb || use_k2 || use_b2;
+        if ((use_k3 || use_b3) && s + 3 <= T && !(two && T - s == 4)) return 3;
         if (two && s + 2 <= T) return 2;
         return 1;
     }
@@ -426,6 +441,9 @@ PassPlan plan_passes(int dtype, int impl, const Geo &g, int32_t T, int32_t tbloc
     // ragged rows (not whole vectors): over x-segments, on grids that are worth it
     const bool ragged = g.nx % (dtype == DCP_F64 ? 2 : 4) != 0;
     if (ragged && g.n < kRaggedMin) return pp;
+    const size_t lds = device_lds();
+    pp.use_b2 = T >= 2 && tblock >= 2 && vok && blk_for(dtype, g, 2, lds, &pp.b2) && (!norms || pp.b2.nblk <= stride);
+    pp.use_b3 = T >= 3 && tblock >= 3 && vok && blk_for(dtype, g, 3, lds, &pp.b3) && (!norms || pp.b3.nblk <= stride);
     pp.use_tb = T >= 2 && !ragged && plan_tb(dtype, g, tblock, vok, &pp.tb) && (!norms || pp.tb.nblk <= stride);
     pp.use_k2 = !pp.use_tb && T >= 2 && tblock >= 2 && plan_tbk(dtype, g, 2, vok, &pp.k2) &&
                 (!norms || pp.k2.nblk <= stride);
@@ -461,11 +479,79 @@ hipError_t tbk_fwd_pass(int dtype, int bc, const Geo &g, const dcp_coeffs &c, co
     return launch_tbk(dtype, bc, part != nullptr, tk, a, st);
 }
 
+// A pass of bk.B steps over blocks u_t -> u_{t+B}; mid and part as above.
+hipError_t blk_fwd_pass(int dtype, int bc, const Geo &g, const dcp_coeffs &c, const BlkTile &bk, const void *u,
+                        const void *f, void *out, void *const mid[2], double *const part[3], hipStream_t st) {
+    BlkArgs a{};
+    a.u = u;
+    a.q[0] = f;
+    a.out = out;
+    for (int i = 0; i < 2; ++i) a.mid[i] = mid ? mid[i] : nullptr;
+    for (int i = 0; i < 3; ++i) a.part[i] = part ? part[i] : nullptr;
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.c0 = c.dt * c.alpha / (c.h * c.h);
+    a.c1 = c.dt * c.beta;
+    a.c2 = c.dt * c.gamma;
+    a.bx = bk.bx;
+    a.by = bk.by;
+    a.tiles_x = bk.tiles_x;
+    a.tiles_y = bk.tiles_y;
+    return launch_blk(dtype, SOP_FWD, bc, part != nullptr, bk, a, st);
+}
+
+// Two adjoint steps per pass, on grids whose rows fit a whole-row tile: over
+// blocks where the grid is small, else over whole rows; nblk = 0 where there
+// are none (or `stride` partial slots are too few).
+struct PairPlan {
+    TbTile tb{};
+    BlkTile bk{};
+    bool blocks = false;
+    int nblk = 0;
+};
+
+PairPlan plan_pair(int dtype, const Geo &g, int32_t tblock, bool vok, int stride) {
+    PairPlan p;
+    if (!plan_tb(dtype, g, tblock, vok, &p.tb)) return p;  // pairs where rows fit a whole-row tile
+    p.blocks = blk_for(dtype, g, 2, device_lds(), &p.bk) && p.bk.nblk <= stride;
+    if (p.blocks) p.nblk = p.bk.nblk;
+    else if (p.tb.nblk <= stride) p.nblk = p.tb.nblk;
+    return p;
+}
+
+hipError_t adj_pair(int dtype, int op, int bc, const PairPlan &p, const TbArgs &ta, hipStream_t st) {
+    if (!p.blocks) return launch_tb2(dtype, op, bc, true, p.tb, ta, st);
+    BlkArgs a{};
+    a.u = ta.u;
+    a.q[0] = ta.f;
+    a.q[1] = ta.g2;
+    a.out = ta.out;
+    a.lam = ta.lam;
+    a.part[0] = ta.part1;
+    a.part[1] = ta.part2;
+    a.nx = ta.nx;
+    a.ny = ta.ny;
+    a.nz = ta.nz;
+    a.c0 = ta.c0;
+    a.c1 = ta.c1;
+    a.bx = p.bk.bx;
+    a.by = p.bk.by;
+    a.tiles_x = p.bk.tiles_x;
+    a.tiles_y = p.bk.tiles_y;
+    a.lam_first = ta.lam_first;
+    return launch_blk(dtype, op, bc, true, p.bk, a, st);
+}
+
 // One forward pass of len (1, 2 or 3) steps without norms, u -> out, in the
 // kernel `pp` plans for that length; mid[i] (when not null) receives the
 // state after i+1 steps of a multi-step pass.
 hipError_t fwd_pass(int dtype, int bc, const Geo &g, const dcp_coeffs &c, const Tile &t, const PassPlan &pp,
                     int len, const void *u, const void *f, void *out, void *mid0, void *mid1, hipStream_t st) {
+    if ((len == 3 && pp.use_b3) || (len == 2 && pp.use_b2)) {
+        void *mid[2] = {mid0, len == 3 ? mid1 : nullptr};
+        return blk_fwd_pass(dtype, bc, g, c, len == 3 ? pp.b3 : pp.b2, u, f, out, mid, nullptr, st);
+    }
     if (len == 3 || (len == 2 && !pp.use_tb)) {
         void *mid[2] = {mid0, len == 3 ? mid1 : nullptr};
         return tbk_fwd_pass(dtype, bc, g, c, len == 3 ? pp.k3 : pp.k2, u, f, out, mid, nullptr, st);
@@ -554,8 +640,10 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         return DCP_OK;
     }
     const size_t fb = align_up(g.bytes());
-    const int nb = max_blocks(dtype, g, kSumBlocks);
+    int nb = max_blocks(dtype, g, kSumBlocks);
     if (nb < 0) return DCP_E_SHAPE;
+    BlkTile bk;
+    if (blk_for(dtype, g, 2, kLdsMax, &bk) && bk.nblk > nb) nb = bk.nblk;
     w->nblk = nb;
     w->origin = off;
     off += fb;
@@ -807,15 +895,18 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
         const int32_t se = s + len;
         void *nxt = is_ckpt(se) ? slot(se / ckpt_every) : ((cur == u) ? buf : u);
         double *p = partials ? partials + (size_t)s * stride * 2 : nullptr;
-        if (len == 3 || (len == 2 && !use_tb)) {
+        const bool blocks = (len == 3 && pp.use_b3) || (len == 2 && pp.use_b2);
+        if (len == 3 || (len == 2 && (blocks || !use_tb))) {
             // checkpoints at the middle steps are stored by the pass itself
             const TbkTile &tk = len == 3 ? tk3 : tk2;
+            const BlkTile &bk = len == 3 ? pp.b3 : pp.b2;
             void *mid[2] = {is_ckpt(s + 1) ? slot((s + 1) / ckpt_every) : nullptr,
                             len == 3 && is_ckpt(s + 2) ? slot((s + 2) / ckpt_every) : nullptr};
             double *part[3] = {p, p ? p + (size_t)stride * 2 : nullptr, p ? p + (size_t)stride * 4 : nullptr};
-            DCP_TRY(tbk_fwd_pass(dtype, bc, g, *coeffs, tk, cur, f, nxt, mid, p ? part : nullptr, st));
+            if (blocks) DCP_TRY(blk_fwd_pass(dtype, bc, g, *coeffs, bk, cur, f, nxt, mid, p ? part : nullptr, st));
+            else DCP_TRY(tbk_fwd_pass(dtype, bc, g, *coeffs, tk, cur, f, nxt, mid, p ? part : nullptr, st));
             if (norms)
-                for (int32_t i = s; i < se; ++i) step_nblk[i] = tk.nblk;
+                for (int32_t i = s; i < se; ++i) step_nblk[i] = blocks ? bk.nblk : tk.nblk;
         } else if (len == 2) {
             // a checkpoint at the middle step is stored by the pass itself
             void *mid = is_ckpt(s + 1) ? slot((s + 1) / ckpt_every) : nullptr;
@@ -867,7 +958,12 @@ int dcp_run_plan(int dtype, int impl, int64_t nx, int64_t ny, int64_t nz, int32_
         s += len;
     }
     info->steps_per_pass = most;
-    if (most >= 2) {
+    if (most >= 2 && (most == 3 ? pp.use_b3 : pp.use_b2)) {
+        const BlkTile &bk = most == 3 ? pp.b3 : pp.b2;
+        info->segmented = bk.bx < g.nx ? 1 : 0;
+        info->tile_rows = bk.by;
+        info->lanes = kBlkLanes;
+    } else if (most >= 2) {
         const bool k = most == 3 || !pp.use_tb;
         const TbkTile &tk = most == 3 ? pp.k3 : pp.k2;
         info->segmented = k && tk.seg ? 1 : 0;
@@ -936,8 +1032,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     double *sums = reinterpret_cast<double *>(at(ws, w.sums));
     const int stride = w.nblk;
     const dcp_coeffs &c = *coeffs;
-    TbTile tb{};
-    const bool use_tb = plan_tb(dtype, g, tblock, vok, &tb) && tb.nblk <= stride;
+    const PairPlan ap = plan_pair(dtype, g, tblock, vok, stride);
     const PassPlan fpp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);  // recomputation
 
     StencilArgs aa{};
@@ -956,8 +1051,8 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     ta.nz = g.nz;
     ta.c0 = aa.c0;
     ta.c1 = aa.c1;
-    ta.nslab = tb.nslab;
-    ta.zc = tb.zc;
+    ta.nslab = ap.tb.nslab;
+    ta.zc = ap.tb.zc;
 
     // Adjoint steps are taken in pairs (2m+1, 2m) by global parity, whatever
     // the checkpoint interval: a pair whose lower step lies in the previous
@@ -991,7 +1086,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
             return seg(tt - t0 - 1);
         };
         while (s >= t0) {
-            const bool pair = use_tb && (s & 1) && s >= 1;
+            const bool pair = ap.nblk && (s & 1) && s >= 1;
             if (pair && s - 1 < t0) break;  // the lower step lives in the previous segment
             const int32_t se = pair ? s - 1 : s;
             void *out = (se == 0) ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
@@ -1004,8 +1099,8 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
                 ta.part1 = partials + (size_t)s * stride * 2;
                 ta.part2 = partials + (size_t)(s - 1) * stride * 2;
                 ta.lam_first = lam_first;
-                DCP_TRY(launch_tb2(dtype, adj_op, bc, true, tb, ta, st));
-                step_nblk[s] = step_nblk[s - 1] = tb.nblk;
+                DCP_TRY(adj_pair(dtype, adj_op, bc, ap, ta, st));
+                step_nblk[s] = step_nblk[s - 1] = ap.nblk;
             } else {
                 aa.s = lcur;
                 aa.q = state(s);
@@ -1167,16 +1262,15 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     aa.c1f = c.dt * c.beta;  // the forward step's coefficients, for the fused recomputation
     aa.c2f = c.dt * c.gamma;
     // two adjoint steps per pass where both states are at hand (tblock >= 2)
-    TbTile tb{};
-    const bool use_tb = tblock >= 2 && plan_tb(dtype, g, tblock, vok, &tb) && tb.nblk <= stride;
+    const PairPlan ap = plan_pair(dtype, g, tblock, vok, stride);
     TbArgs ta{};
     ta.nx = g.nx;
     ta.ny = g.ny;
     ta.nz = g.nz;
     ta.c0 = aa.c0;
     ta.c1 = aa.c1;
-    ta.nslab = tb.nslab;
-    ta.zc = tb.zc;
+    ta.nslab = ap.tb.nslab;
+    ta.zc = ap.tb.zc;
     ta.lam = lsum;
     std::vector<int> step_nblk((size_t)T, t.nblk);
     const int adj_op = lsum ? SOP_ADJL : SOP_ADJ;
@@ -1237,7 +1331,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
         // or steps s and s - 1 when the next operation is step s - 1
         const RvOp &adj = folded ? ops[i + 1] : op;
         const int64_t s = adj.t0;
-        const bool pair = !folded && use_tb && i + 1 < ops.size() && ops[i + 1].kind == kRvAdjoint &&
+        const bool pair = !folded && ap.nblk && i + 1 < ops.size() && ops[i + 1].kind == kRvAdjoint &&
                           ops[i + 1].t0 == s - 1;
         const int64_t se = pair ? s - 1 : s;
         void *out = (se == 0) ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
@@ -1250,8 +1344,8 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
             ta.part1 = partials + (size_t)s * stride * 2;
             ta.part2 = partials + (size_t)(s - 1) * stride * 2;
             ta.lam_first = lam_first;
-            DCP_TRY(launch_tb2(dtype, adj_op, bc, true, tb, ta, st));
-            step_nblk[s] = step_nblk[s - 1] = tb.nblk;
+            DCP_TRY(adj_pair(dtype, adj_op, bc, ap, ta, st));
+            step_nblk[s] = step_nblk[s - 1] = ap.nblk;
         } else {
             aa.s = lcur;
             aa.q = folded ? f : B.buf(adj.src);

@@ -165,6 +165,28 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
               int force_wc, int force_ty, TbkTile *t);
 hipError_t launch_tbk(int dtype, int bc, bool reduce, const TbkTile &t, const TbkArgs &a, hipStream_t stream);
 
+// B fused steps per pass (2 or 3; the adjoint 2) on blocks of bx x by x bz
+// points with a halo of B on every side, for small grids (dcp_block.hip).
+struct BlkArgs {
+    const void *u;     // level 0: u_t, or lambda_{t+1}
+    const void *q[2];  // point operands: f; or u_t and u_{t-1}
+    void *out;
+    void *mid[2];      // middle states, or null
+    void *lam;         // SOP_ADJL: running sum of the adjoint inputs
+    double *part[3];   // the B steps' sums, [nblk][2] each
+    int64_t nx, ny, nz;
+    double c0, c1, c2;
+    int bx, by, tiles_x, tiles_y, lam_first;
+};
+struct BlkTile {
+    int B, bx, by, bz, tiles_x, tiles_y, nblk;
+    size_t lds;
+};
+constexpr int kBlkLanes = 768;
+// Plans a B-step pass; false if the grid is too large for blocks to pay.
+bool blk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, size_t lds_limit, BlkTile *t);
+hipError_t launch_blk(int dtype, int op, int bc, bool reduce, const BlkTile &t, const BlkArgs &a, hipStream_t st);
+
 // Fixed-order reduction of [nsteps][stride][2] partials (first nblk used).
 //   mode 0: out0[0] = sum k=0, out0[1] = sum k=1          (one step)
 //   mode 1: out0[s] = sum k=0, out1[s] = sqrt(sum k=1)   (either may be null)

@@ -61,9 +61,10 @@ def test_single_steps_and_their_adjoint(dtype, nx, bc):
         assert abs(float(g["gamma"]) - w["gamma"]) <= TOL[dtype] * 0.1 * n
 
 
-# at least 2^18 points, so that runs take passes of several steps: two and more
-# segments, a short last one, few rows, few planes
-SHAPES = [(257, 40, 37), (131, 70, 35), (1031, 20, 17), (515, 33, 20), (2051, 13, 11), (513, 513, 3), (37, 97, 80),
+# at least 2^18 points, so that runs take passes of several steps (the first
+# ones over blocks, those of more than about 900,000 points over x-segments):
+# two and more segments, a short last one, few rows, few planes
+SHAPES = [(257, 80, 61), (1031, 40, 33), (515, 66, 40), (129, 129, 70), (2051, 33, 17), (97, 333, 40), (513, 700, 3), (257, 40, 37), (131, 70, 35), (1031, 20, 17), (515, 33, 20), (2051, 13, 11), (513, 513, 3), (37, 97, 80),
           (1022, 21, 13)]
 
 
