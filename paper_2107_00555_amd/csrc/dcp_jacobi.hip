@@ -44,8 +44,9 @@ struct J1Args {
     const double *ain, *bin, *bfix;
     double *aout, *bout;
     int64_t n, inner;
-    int hh, nhalf, phase;  // halo, half-steps in this pass, 1 = first half-step writes A
+    int hh, nhalf, phase;  // halo of a region, half-steps in this pass, 1 = first half-step writes A
     int write_b;
+    int align;  // regions are placed so that the array's ends start or end a lane's run
 };
 
 // vec16: every lane's two columns are one aligned 16-byte pair (n1 and hh
@@ -112,47 +113,60 @@ __global__ void __launch_bounds__(64) j1_kernel(J1Args a) {
     __shared__ double stage[64 * (K + 1)];
     const int lane = threadIdx.x;
     const int64_t n = a.n;
-    const int64_t rbase = (int64_t)blockIdx.x * a.inner - a.hh;  // global index of region cell 0
+    // Global index of region cell 0.  With a.align (arrays whose waves all run
+    // at once, so that a pass is as long as its slowest wave) a region that holds
+    // the array's last cell moves left until that cell ends a lane's run; the
+    // first cell starts one (a.hh and a.inner are whole runs then, and a.hh has
+    // room for the move).
+    int64_t rbase = (int64_t)blockIdx.x * a.inner - a.hh;
+    const int64_t own0 = rbase + a.hh;  // the tile: [own0, own0 + inner)
+    if (a.align && rbase + R >= n) {
+        const int64_t m = (rbase - n) % K;
+        rbase -= m < 0 ? m + K : m;
+    }
     const int64_t g0 = rbase + (int64_t)lane * K;
     auto pos = [](int i) { return i + i / K; };
 
+    // cells outside the array read its nearest end: they only feed the end
+    // cell, which is kept, and each other
+    auto fetch = [&](const double *src, double(&x)[K]) __attribute__((always_inline)) {
+        double v[K];
+#pragma unroll
+        for (int m = 0; m < K; ++m) v[m] = src[min(max(rbase + m * 64 + lane, (int64_t)0), n - 1)];
+#pragma unroll
+        for (int m = 0; m < K; ++m) stage[pos(m * 64 + lane)] = v[m];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = stage[lane * (K + 1) + k];
+    };
     double va[K], vb[K];
-#pragma unroll
-    for (int m = 0; m < K; ++m) {
-        const int i = m * 64 + lane;
-        const int64_t g = rbase + i;
-        stage[pos(i)] = (g >= 0 && g < n) ? a.ain[g] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) va[k] = stage[lane * (K + 1) + k];
+    // B's interior is written before it is read when the pass starts with B:
+    // only its ends matter
+    const double b0 = a.bfix[0], b1 = a.bfix[n - 1];
+    fetch(a.ain, va);
     if (a.phase) {
         __syncthreads();
-#pragma unroll
-        for (int m = 0; m < K; ++m) {
-            const int i = m * 64 + lane;
-            const int64_t g = rbase + i;
-            stage[pos(i)] = (g >= 0 && g < n) ? a.bin[g] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < K; ++k) vb[k] = stage[lane * (K + 1) + k];
+        fetch(a.bin, vb);
     } else {
-        // B's interior is written before it is read; only its ends matter
 #pragma unroll
-        for (int k = 0; k < K; ++k) vb[k] = 0.0;
-        if (rbase <= 0 || rbase + R >= n) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int64_t g = g0 + k;
-                if (g == 0 || g == n - 1) vb[k] = a.bfix[g];
-            }
-        }
+        for (int k = 0; k < K; ++k) vb[k] = g0 + k <= 0 ? b0 : g0 + k >= n - 1 ? b1 : 0.0;
     }
-    // the ends of the array, 0 and n-1, fall in this region only for the
-    // first and last workgroups
+    // The ends of the array keep their values.  They fall in this region only
+    // for the first and last workgroups, as the first and the last point of a
+    // lane's run where the region is placed for that: two selects per
+    // half-step.  Otherwise every point takes one (a select per point doubles
+    // the half-step, and with it a pass whose waves all run at once).
     const bool edge = rbase <= 0 || rbase + R - 1 >= n - 1;
-    auto half = [&](double(&d)[K], const double(&s)[K], auto masked) __attribute__((always_inline)) {
+    const bool aligned = a.align && (rbase > 0 || rbase % K == 0) && (rbase + R < n || (n - rbase) % K == 0);
+    uint64_t keep[K];
+    if (edge) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) keep[k] = __builtin_amdgcn_ballot_w64(g0 + k == 0 || g0 + k == n - 1);
+    }
+    // PLAIN: no end in the region; ENDS: at the first or last point of a run
+    enum { PLAIN, ENDS, ANY };
+    auto half = [&](double(&d)[K], const double(&s)[K], auto mode) __attribute__((always_inline)) {
+        constexpr int M = decltype(mode)::value;
         const double left = from_lower(s[K - 1]);
         const double right = from_upper(s[0]);
 #pragma unroll
@@ -160,28 +174,26 @@ __global__ void __launch_bounds__(64) j1_kernel(J1Args a) {
             const double l = k == 0 ? left : s[k > 0 ? k - 1 : 0];
             const double r = k == K - 1 ? right : s[k < K - 1 ? k + 1 : k];
             const double nv = kW1 * ((l + s[k]) + r);
-            if constexpr (decltype(masked)::value) {
-                const int64_t g = g0 + k;
-                d[k] = j_keep(__builtin_amdgcn_ballot_w64(g == 0 || g == n - 1), nv, d[k]);
-            } else {
-                d[k] = nv;
-            }
+            if constexpr (M == ANY) d[k] = j_keep(keep[k], nv, d[k]);
+            else if constexpr (M == ENDS) d[k] = k == 0 || k == K - 1 ? j_keep(keep[k], nv, d[k]) : nv;
+            else d[k] = nv;
         }
     };
-    auto steps = [&](auto masked) __attribute__((always_inline)) {
+    auto steps = [&](auto mode) __attribute__((always_inline)) {
         int s = 0;
         if (a.phase && a.nhalf > 0) {
-            half(va, vb, masked);
+            half(va, vb, mode);
             s = 1;
         }
         for (; s + 2 <= a.nhalf; s += 2) {
-            half(vb, va, masked);
-            half(va, vb, masked);
+            half(vb, va, mode);
+            half(va, vb, mode);
         }
-        if (s < a.nhalf) half(vb, va, masked);
+        if (s < a.nhalf) half(vb, va, mode);
     };
-    if (edge) steps(std::true_type{});
-    else steps(std::false_type{});
+    if (!edge) steps(std::integral_constant<int, PLAIN>{});
+    else if (aligned) steps(std::integral_constant<int, ENDS>{});
+    else steps(std::integral_constant<int, ANY>{});
 
     // write the tile: A, then (if it is needed) B, each through the LDS
     // transpose
@@ -197,7 +209,7 @@ __global__ void __launch_bounds__(64) j1_kernel(J1Args a) {
         for (int m = 0; m < K; ++m) {
             const int i = m * 64 + lane;
             const int64_t g = rbase + i;
-            if (i >= a.hh && i < R - a.hh && g >= lo && g < hi) out[g] = stage[pos(i)];
+            if (g >= max(own0, lo) && g < min(own0 + a.inner, hi)) out[g] = stage[pos(i)];
         }
     }
 }
@@ -564,6 +576,10 @@ constexpr size_t kJAlign = 256;
 // array gives at least 2048 workgroups with them.  Smaller arrays take the
 // shortest admissible run (tile at least half the region), spreading the
 // work over more CUs.  DCP_J1_K forces a length (tuning runs only).
+// Halo of a region placed by the array's ends (see j1_kernel): whole runs, with
+// room to move the region by less than one.
+int64_t j1_halo(int64_t K, int64_t hh) { return (hh + 2 * (K - 1)) / K * K; }
+
 int j1_pick_k(int64_t n, int64_t hh) {
     auto admissible = [&](int k) { return 64 * k - 2 * hh >= 32 * k; };
     const char *forced = dcp::tuning_env("DCP_J1_K");
@@ -822,14 +838,18 @@ int dcp_jacobi_1d(int32_t tsteps, double *A, double *B, int64_t n, int32_t tbloc
     st = j_check_buffers(g, A, B, ws, ws_bytes, j_ws_need(g, p));
     if (st != DCP_OK || p.passes == 0) return st;
     const int K = j1_pick_k(n, p.hh);
-    const int64_t inner = 64 * K - 2 * p.hh;
+    // the wider halo costs about 6% more waves: worth it while they run at once
+    // (T = 1000, n = 24,000: 209 us with a select per point at the ends, 177
+    // with two; n = 300,001: 323 and 310; n = 10^6: 655 and 674)
+    const bool align = K <= 8 && 64 * K > 2 * j1_halo(K, p.hh) && n / (64 * K - 2 * p.hh) < 4096;
+    const int64_t hr = align ? j1_halo(K, p.hh) : p.hh, inner = 64 * K - 2 * hr;
     const int64_t blocks = (n + inner - 1) / inner;
     if (blocks > INT32_MAX) return DCP_E_SHAPE;
     hipStream_t sm = static_cast<hipStream_t>(stream);
     return j_run_passes(g, p, A, B, ws,
                         [&](const double *ain, const double *bin, const double *bfix, double *aout, double *bout,
                             int nh, int ph, int wb) {
-                            const J1Args a{ain, bin, bfix, aout, bout, n, inner, (int)p.hh, nh, ph, wb};
+                            const J1Args a{ain, bin, bfix, aout, bout, n, inner, (int)hr, nh, ph, wb, align ? 1 : 0};
                             switch (K) {
                                 case 4: return j1_launch<4>(blocks, a, sm);
                                 case 8: return j1_launch<8>(blocks, a, sm);
