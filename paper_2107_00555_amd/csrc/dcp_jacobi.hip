@@ -390,8 +390,7 @@ __global__ void __launch_bounds__(1024, RPL <= 4 ? 8 : 4) j2_kernel(J2Args a) {
 // The array's boundary cells keep their values at every level: level s takes
 // them from level s - 2 (the same array; the slot it is about to leave behind
 // still holds that row), level 1 from B in memory.  A wave that holds no
-// boundary cell skips all of this.  Requires n1 even, hh even and 16-byte
-// aligned arrays.
+// boundary cell skips all of this.  Requires hh even.
 // What bounds it: FP64 issue (5 operations per cell and four 32-bit DPP moves
 // per pair, on 128 / (128 - 2 hh) of the columns), then memory: 23400^2 with
 // 16 half-steps takes 183 us per half-step; the same kernel without loads and
@@ -400,7 +399,7 @@ __global__ void __launch_bounds__(1024, RPL <= 4 ? 8 : 4) j2_kernel(J2Args a) {
 // pass.  Four columns per lane need fewer moves per cell, but fit only 8
 // half-steps with rows fetched one ahead, and waited on memory: 266 us per
 // half-step, 254 with the boundary selects taken out.
-typedef double j2m_v2 __attribute__((ext_vector_type(2)));
+typedef double j2m_v2 __attribute__((ext_vector_type(2), aligned(8)));  // rows of any length
 
 struct J2MArgs {
     const double *ain, *bfix;  // level 0 (A); B's values (its boundary cells never change)
@@ -447,12 +446,14 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
     const int n1 = (int)a.n1;
     const int ci = CPL * lane;                           // column offset in the strip
     const int gc = strip * (C - 2 * a.hh) - a.hh + ci;   // column of this lane's first value (even)
-    // the lane's two columns are in the array both or neither; their load
-    // column, clamped into the array; whether this strip stores them
+    // the lane's load column, clamped into the array, and whether this strip
+    // stores its columns; with an odd n1 the last column is the first of a
+    // lane's two (`last`: it loads them one column early and stores one)
     const int col = min(max(gc, 0), n1 - 2);
     const bool own = gc >= 0 && gc < n1 && ci >= a.hh && ci < C - a.hh;
-    // lanes whose first column is 0, whose second is n1 - 1 (n1 and gc even)
-    const uint64_t keep[CPL] = {__builtin_amdgcn_ballot_w64(gc == 0), __builtin_amdgcn_ballot_w64(gc == n1 - 2)};
+    const bool last = gc == n1 - 1;
+    // lanes whose first column is 0 or n1 - 1, whose second is n1 - 1
+    const uint64_t keep[CPL] = {__builtin_amdgcn_ballot_w64(gc == 0 || last), __builtin_amdgcn_ballot_w64(gc == n1 - 2)};
     const bool edge = (keep[0] | keep[1]) != 0;  // uniform over the wave
     const int R0 = seg * a.seg_rows;
     const int R1 = min(n0, R0 + a.seg_rows);
@@ -465,6 +466,8 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
         x[0] = v.x;
         x[1] = v.y;
     };
+    // the column a `last` lane needs is the second of the pair it loaded
+    auto fix_last = [&](double (&x)[CPL]) { x[0] = last ? x[1] : x[0]; };
 
     double S[NH][3][CPL];  // [level][row slot: row mod 3, counted from q0][column]
     double P[D][CPL];      // level-0 rows in flight
@@ -479,6 +482,8 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
     // level 0: rows q0 - 1 and q0 now, rows q0 + 1 .. q0 + D in flight
     load_row(a.ain, q0 - 1, S[0][2]);
     load_row(a.ain, q0, S[0][0]);
+    fix_last(S[0][2]);
+    fix_last(S[0][0]);
     const bool general_wave = edge || rowedge;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -497,6 +502,7 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
         double(&pf)[CPL] = P[(ph + 1) % D];
 #pragma unroll
         for (int k = 0; k < CPL; ++k) l0[k] = pf[k];
+        if constexpr (general) fix_last(l0);
         load_row(a.ain, q + 1 + D, pf);
 #pragma unroll
         for (int s = 1; s <= NH; ++s) {
@@ -519,6 +525,7 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
             if constexpr (general) {
                 // boundary cells of row r keep their values: those of level
                 // s - 2 (level 0 and up), of B in memory (level 1)
+                if (s == 1) fix_last(PB[ph]);
                 const double(&old)[CPL] = s == 1 ? PB[ph] : S[s >= 2 ? s - 2 : 0][mid];
                 const bool frow = r == 0 || r == n0 - 1;  // uniform: the whole row
 #pragma unroll
@@ -531,16 +538,19 @@ __global__ void __launch_bounds__(64) j2m_kernel(J2MArgs a) {
             // A's row r is stored where it belongs to the segment, B's row
             // (the level before) by the last pass only; a store covers whole
             // lines and goes out with the streaming hint
-            if (s == NH && r >= R0 && own)
-                __builtin_nontemporal_store(j2m_v2{nv[0], nv[1]},
-                                            reinterpret_cast<j2m_v2 *>(a.aout + (int64_t)r * n1 + gc));
+            if (s == NH && r >= R0 && own) {
+                double *o = a.aout + (int64_t)r * n1 + gc;
+                if (general && last) *o = nv[0];
+                else __builtin_nontemporal_store(j2m_v2{nv[0], nv[1]}, reinterpret_cast<j2m_v2 *>(o));
+            }
             if (s == NH - 1 && a.write_b != 0 && r >= R0 && r < R1 && own) {
-                const int64_t o = (int64_t)r * n1 + gc;
+                double *o = a.bout + (int64_t)r * n1 + gc;
                 if (a.write_b == 1) {
-                    __builtin_nontemporal_store(j2m_v2{nv[0], nv[1]}, reinterpret_cast<j2m_v2 *>(a.bout + o));
+                    if (general && last) *o = nv[0];
+                    else __builtin_nontemporal_store(j2m_v2{nv[0], nv[1]}, reinterpret_cast<j2m_v2 *>(o));
                 } else if (r >= 1 && r <= n0 - 2) {  // B's interior only
-                    if (gc >= 1) a.bout[o] = nv[0];
-                    if (gc + 1 <= n1 - 2) a.bout[o + 1] = nv[1];
+                    if (gc >= 1 && !last) o[0] = nv[0];
+                    if (gc + 1 <= n1 - 2) o[1] = nv[1];
                 }
             }
         }
@@ -628,9 +638,8 @@ int j2_pick_rpl(int64_t n0, int64_t n1, int64_t hh) {
 }
 
 // The row-marching form (j2m_kernel): used for arrays that give it at least
-// 2048 waves (two per SIMD) with row segments of at least 4*NH rows, when n1
-// is even and the arrays are 16-byte aligned; passes of 4 to 16 half-steps
-// (even) that start with B (whole time-loop iterations).  More, shorter
+// 2048 waves (two per SIMD) with row segments of at least 4*NH rows; passes of
+// 4 to 16 half-steps (even) that start with B (whole time-loop iterations).  More, shorter
 // segments even out the end of a pass (a share of about 2048 / waves of it)
 // but recompute 2*NH rows each; their sum is least near
 // sqrt(768 * n0 * strips / NH) waves.  Measured with 16 half-steps, us per
@@ -647,7 +656,7 @@ struct J2MPlan {
 J2MPlan j2m_pick(int64_t n0, int64_t n1, int64_t hh) {
     J2MPlan m;
     constexpr int64_t C = 128;
-    if (n0 < 3 || n1 < 3 || n0 >= ((int64_t)1 << 30) || n1 % 2 != 0 || hh % 2 != 0 || hh < 4 || hh > 16)
+    if (n0 < 3 || n1 < 3 || n0 >= ((int64_t)1 << 30) || hh % 2 != 0 || hh < 4 || hh > 16)
         return m;
     const int64_t strips = (n1 + (C - 2 * hh) - 1) / (C - 2 * hh);
     const int64_t maxsegs = std::max<int64_t>(1, n0 / (4 * hh));
@@ -910,7 +919,7 @@ int dcp_jacobi_2d(int32_t tsteps, double *A, double *B, int64_t n0, int64_t n1, 
                                               (uintptr_t)aout | (uintptr_t)bout) % 16 == 0;
                             // whole iterations (B first, B's interior not read):
                             // the row-marching form
-                            if (mp.use && v16 && p.whole && ph == 0 && nh >= 4 && nh <= 16 && nh % 2 == 0) {
+                            if (mp.use && p.whole && ph == 0 && nh >= 4 && nh <= 16 && nh % 2 == 0) {
                                 const J2MArgs m{ain, bfix, aout, bout, n0, n1, (int)p.hh, mp.strips, mp.segs,
                                                 mp.seg_rows, wb};
                                 return launch_march(m, nh);

@@ -135,11 +135,13 @@ def test_jacobi_2d_region_tile_heights(shape, tblock):
 
 
 @pytest.mark.parametrize("shape,tblock", [((400, 484), 16), ((401, 566), 8), ((257, 388), 16), ((193, 674), 10),
-                                          ((130, 416), 4)])
+                                          ((130, 416), 4), ((300, 401), 16), ((1201, 1001), 8), ((77, 129), 16),
+                                          ((500, 97), 12), ((400, 485), 16), ((401, 567), 8), ((65, 3), 6), ((66, 5), 4)])
 def test_jacobi_2d_marching_tile_order(monkeypatch, shape, tblock):
     """Several strips and segments, the workgroups that hold boundary cells
     numbered first: the last column inside the halo of the last strip but one,
-    a last segment shorter than a pass.  Bit for bit against the oracle."""
+    a last segment shorter than a pass; rows of odd length, whose last column
+    is the first of a lane's two.  Bit for bit against the oracle."""
     monkeypatch.setenv("DCP_TUNING", "1")
     monkeypatch.setenv("DCP_J2_MODE", "3")
     A, B = inputs.jacobi_fields(2, shape[0], seed=11, n1=shape[1])
