@@ -452,7 +452,15 @@ __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
 // Ring slots are (plane - q0) mod 3, compile-time constants in a plane loop
 // unrolled three times, so no register copies rotate the queues.  Every
 // point is computed with the one-step kernel's operations, as in tbk_kernel.
-template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED>
+// MID: the middle states are stored too, those that are not null; a pass
+// without any is compiled without those stores.
+// Bound: at 512^3 a pass moves 2.1 GiB in FP64 and its arithmetic and LDS
+// accesses take 0.44 ms of 0.61 from a warm L2, so the rest is how well loads
+// run under it.  99 steps at 512^3 (FP64 / FP32, ms): 21.3 / 11.7 before,
+// 20.7 / 11.3 with the wave-edge neighbours read beside the y-neighbours,
+// 20.4 / 11.2 with scalar plane bases, 20.0 / 11.0 with every store
+// unconditional, whose waits the compiler counts exactly.
+template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED, bool MID>
 __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     static_assert(B >= 2 && B <= 3, "two or three steps per pass");
     extern __shared__ __align__(16) unsigned char tbk_smem[];
@@ -496,7 +504,6 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
 
     const T *__restrict__ U = static_cast<const T *>(a.u);
     const T *__restrict__ F = static_cast<const T *>(a.f);
-    T *__restrict__ O = static_cast<T *>(a.out);
     const T C0 = (T)a.c0, C1 = (T)a.c1, C2 = (T)a.c2;
 
     int lofs[KM], gofs[KM];
@@ -537,6 +544,25 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     auto at = [&](const T *plane, int k) -> const T * {
         return reinterpret_cast<const T *>(reinterpret_cast<const char *>(plane) + gb[k]);
     };
+    // Every lane also stores, to a buffer of one plane: what lies past its bound
+    // is dropped (chunks the tile does not own, planes it does not, a middle
+    // state that is not wanted).  Stores under a condition are stores the waits
+    // cannot count: waiting for a load then waits for the stores before it.
+    typedef unsigned kq_t __attribute__((ext_vector_type(4)));
+    const unsigned plane_bytes = (unsigned)(sz * (int64_t)sizeof(T));
+    unsigned sb[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) sb[k] = flags[k] & kOwned ? gb[k] : ~0u;
+    auto sink_of = [&](void *field, int p, bool on) {
+        T *base = static_cast<T *>(field) + (int64_t)(on ? p : 0) * sz;
+        return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, on && field ? plane_bytes : 0u, 0x00027000);
+    };
+    auto store_own = [&](auto sink, int k, const T (&r)[VEC]) {
+        typename KVec<T, VEC>::type v;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = r[e];
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(kq_t, v), sink, sb[k], 0, 2 /* streaming */);
+    };
     auto load_u = [&](int zq, T (&d)[KM][VEC]) {
         const int zr = k_wrap<BC>(zq, nz);
         const T *plane = U + (int64_t)(zr >= 0 ? zr : 0) * sz;
@@ -565,15 +591,21 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
             }
         }
     };
-    auto xnbrs = [&](const T *base, int o, int c, const T (&v)[VEC], T &lft, T &rgt) {
+    // x-neighbours of a chunk: across the wave from the adjacent lanes' registers;
+    // the wave's first and last lane from LDS, by one read that every lane makes
+    // at the same time as its y-neighbours' (a read under a condition is a wait
+    // of its own).  Past a segment's frame they are never needed; a whole row
+    // wraps (periodic) or reads 0.
+    const int eofs = wlane == 0 ? -1 : wlane == 63 ? VEC : 0;
+    auto xnbrs = [&](const T *base, int o, int c, const T (&v)[VEC], T edge, T &lft, T &rgt) {
         const T fl = k_dpp<0x138>(v[VEC - 1]);
         const T fu = k_dpp<0x130>(v[0]);
-        if (c > 0) lft = wlane != 0 ? fl : base[o - 1];
-        else if (!SEG && BC == 1) lft = base[o + FW - 1];
-        else lft = T(0);
-        if (c < CHF - 1) rgt = wlane != 63 ? fu : base[o + VEC];
-        else if (!SEG && BC == 1) rgt = base[o - c * VEC];
-        else rgt = T(0);
+        lft = wlane == 0 ? edge : fl;
+        rgt = wlane == 63 ? edge : fu;
+        if constexpr (!SEG) {
+            if (c == 0) lft = BC == 1 ? base[o + FW - 1] : T(0);
+            if (c == CHF - 1) rgt = BC == 1 ? base[o - c * VEC] : T(0);
+        }
     };
 
     // a point's value in the norms: 0 where the segment before counts it
@@ -622,16 +654,19 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
 
     auto iter = [&](auto phc, const int q) {
         constexpr int PH = decltype(phc)::value;
+        // keep the 64-bit form of the offsets out of the registers (it frees 18,
+        // and the accesses take the plane from scalar registers)
+#pragma unroll
+        for (int k = 0; k < KM; ++k) asm volatile("" : "+v"(gb[k]));
         ghost0(q + 1, RU[rs3(PH + 1)]);
 #pragma unroll
         for (int s = 1; s <= B; ++s) {
-            if (q < q0 + 2 * (s - 1)) continue;  // stage s starts two planes after stage s-1
-            const int p = q - s + 1;               // plane of level s
+            const int p = q - s + 1;  // plane of level s
             const bool owned_plane = p >= z0 && p < z1;
             const int pr = k_wrap<BC>(p, nz);
             const T *src = s == 1 ? L0p(q) : LSp(s - 1, p);
             T *dst = s < B ? LSp(s, p) : nullptr;
-            T *mid = s < B ? static_cast<T *>(a.mid[s - 1]) : nullptr;
+            const auto sink = sink_of(s < B ? a.mid[s < B ? s - 1 : 0] : a.out, p, owned_plane);
             // level s-1 at planes p-1, p, p+1 (registers), level s at p (result)
             T(&Lm)[KM][VEC] = s == 1 ? RU[rs3(PH - 1)] : RZ[s >= 2 ? s - 2 : 0][rs3(PH - s)];
             T(&Lc)[KM][VEC] = s == 1 ? RU[rs3(PH)] : RZ[s >= 2 ? s - 2 : 0][rs3(PH + 1 - s)];
@@ -642,44 +677,42 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
 #pragma unroll
             for (int k = 0; k < KM; ++k) {
                 const unsigned fl = flags[k];
-                if (!(fl & (1u << s))) continue;
-                const int o = lofs[k];
-                T ym[VEC], yp[VEC], f3[VEC], lft, rgt;
-                k_load<T, VEC>(ym, src + o - FW);
-                k_load<T, VEC>(yp, src + o + FW);
-                if (s == 3) k_load<T, VEC>(f3, FB + o);
-                xnbrs(src, o, (int)(fl >> kColShift), Lc[k], lft, rgt);
                 T res[VEC];
-                if (s < B && BC == 0 && (pr < 0 || (fl & kGhost))) {
-                    k_zero<T, VEC>(res);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const T xm = e == 0 ? lft : Lc[k][e > 0 ? e - 1 : 0];
-                        const T xp = e == VEC - 1 ? rgt : Lc[k][e + 1 < VEC ? e + 1 : e];
-                        const T fq = s == 1 ? RF[rs3(PH)][k][e] : s == 2 ? RF[rs3(PH - 1)][k][e] : f3[e];
-                        res[e] = k_fwd<T>(Lc[k][e], xm, xp, ym[e], yp[e], Lm[k][e], Lp[k][e], fq, C0, C1, C2);
-                    }
-                }
-                const bool here = (fl & kOwned) && owned_plane;
-                if (s < B) {
-                    k_store<T, VEC>(dst + o, res);
-                    k_copy<T, VEC>(Lo[k], res);
-                    if (mid && here) k_gstore_nt<T, VEC>(const_cast<T *>(at(mid + (int64_t)p * sz, k)), res);
-                } else if (fl & kOwned) {
-                    k_gstore_nt<T, VEC>(const_cast<T *>(at(O + (int64_t)p * sz, k)), res);
-                }
-                if constexpr (RED) {
-                    if (here) {
+                k_zero<T, VEC>(res);
+                if (fl & (1u << s)) {
+                    const int o = lofs[k];
+                    T ym[VEC], yp[VEC], f3[VEC], lft, rgt;
+                    k_load<T, VEC>(ym, src + o - FW);
+                    k_load<T, VEC>(yp, src + o + FW);
+                    const T edge = src[o + eofs];
+                    if (s == 3) k_load<T, VEC>(f3, FB + o);
+                    xnbrs(src, o, (int)(fl >> kColShift), Lc[k], edge, lft, rgt);
+                    if (!(s < B && BC == 0 && (pr < 0 || (fl & kGhost)))) {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
-                            const double d = counts(fl, e, res[e]);
-                            es[s - 1] = fma(d, d, es[s - 1]);
-                            const double dd = d - counts(fl, e, Lc[k][e]);
-                            rs[s - 1] = fma(dd, dd, rs[s - 1]);
+                            const T xm = e == 0 ? lft : Lc[k][e > 0 ? e - 1 : 0];
+                            const T xp = e == VEC - 1 ? rgt : Lc[k][e + 1 < VEC ? e + 1 : e];
+                            const T fq = s == 1 ? RF[rs3(PH)][k][e] : s == 2 ? RF[rs3(PH - 1)][k][e] : f3[e];
+                            res[e] = k_fwd<T>(Lc[k][e], xm, xp, ym[e], yp[e], Lm[k][e], Lp[k][e], fq, C0, C1, C2);
+                        }
+                    }
+                    if (s < B) {
+                        k_store<T, VEC>(dst + o, res);
+                        k_copy<T, VEC>(Lo[k], res);
+                    }
+                    if constexpr (RED) {
+                        if ((fl & kOwned) && owned_plane) {
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) {
+                                const double d = counts(fl, e, res[e]);
+                                es[s - 1] = fma(d, d, es[s - 1]);
+                                const double dd = d - counts(fl, e, Lc[k][e]);
+                                rs[s - 1] = fma(dd, dd, rs[s - 1]);
+                            }
                         }
                     }
                 }
+                if (s == B || MID) store_own(sink, k, res);
             }
             // level 0 at q-1 is dead: fetch plane q+2 into its slot
             if (s == 1) load_u(q + 2, RU[rs3(PH + 2)]);
@@ -750,9 +783,9 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     }
 }
 
-template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED, bool RING>
+template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED, bool MID, bool RING>
 auto tbk_fn() {
-    if constexpr (RING) return tbr_kernel<T, VEC, B, NT, KM, BC, SEG, RAG, RED>;
+    if constexpr (RING) return tbr_kernel<T, VEC, B, NT, KM, BC, SEG, RAG, RED, MID>;
     else return tbk_kernel<T, VEC, B, NT, KM, BC, SEG, RAG, RED>;
 }
 
@@ -760,13 +793,23 @@ template <typename T, int VEC, int B, int NT, int KM, bool RING>
 hipError_t tbk_launch_t(int bc, bool reduce, const TbkTile &t, const TbkArgs &a, hipStream_t st) {
     const dim3 grid(t.nblk), block(NT);
     const size_t lds = t.lds_bytes;
-#define DCP_TBK(BCV, SEGV, RAGV, REDV)                                                               \
+    const bool mid = a.mid[0] || a.mid[1];  // two-step ring passes take the form that stores them
+#define DCP_TBK_MID(BCV, SEGV, RAGV, REDV, MIDV)                                                     \
     do {                                                                                             \
-        auto fn = tbk_fn<T, VEC, B, NT, KM, BCV, SEGV, RAGV, REDV, RING>();                          \
+        auto fn = tbk_fn<T, VEC, B, NT, KM, BCV, SEGV, RAGV, REDV, MIDV, RING>();                    \
         hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),                      \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);   \
         if (e_ != hipSuccess) return e_;                                                             \
         hipLaunchKernelGGL(fn, grid, block, lds, st, a);                                             \
+    } while (0)
+#define DCP_TBK(BCV, SEGV, RAGV, REDV)                                              \
+    do {                                                                             \
+        if constexpr (RING && B == 3) {                                              \
+            if (mid) DCP_TBK_MID(BCV, SEGV, RAGV, REDV, true);                       \
+            else DCP_TBK_MID(BCV, SEGV, RAGV, REDV, false);                          \
+        } else {                                                                     \
+            DCP_TBK_MID(BCV, SEGV, RAGV, REDV, true);                                \
+        }                                                                            \
     } while (0)
 #define DCP_TBK_RED(BCV, SEGV, RAGV)                \
     do {                                            \
@@ -790,6 +833,7 @@ hipError_t tbk_launch_t(int bc, bool reduce, const TbkTile &t, const TbkArgs &a,
     }
 #undef DCP_TBK_RED
 #undef DCP_TBK
+#undef DCP_TBK_MID
     return hipGetLastError();
 }
 
