@@ -571,17 +571,15 @@ void generate(dcp_fused *p) {
                 for (int q = 0; q < span; ++q)
                     b << "        " << T << " Q" << g << "_" << q << "[V];\n"
                       << "        bool W" << g << "_" << q << " = " << slot_fn(g) << "(m" << grps[g].field << ", Q"
-                      << g << "_" << q << ", xc, y + (" << grps[g].dy << "), zb + (" << grps[g].dzlo + q
+                      << g << "_" << q << ", x, y + (" << grps[g].dy << "), zb + (" << grps[g].dzlo + q
                       << "), nx, ny, nz, bc);\n";
                 b << "        " << T << " P" << g << "[V];\n";
             }
-            b << "        for (I z = zb; z < ze; ++z, i += plane) {\n"
-              // a lane past a ragged row end (V points not all in the row)
-              << "            const bool rg = x + V > nx;\n"
-              << "            const unsigned long long mrg = __builtin_amdgcn_ballot_w64(rg);\n";
+            b << "        for (I z = zb; z < ze; ++z, i += plane) {\n";
             // per read: the elements from outside the lane at a wave or row
-            // end (one load each, into scalars of their own), and, in a wave
-            // with a ragged lane, that lane's points through the rule
+            // end (one load each, into scalars of their own); the lane of a
+            // ragged row's last points and its lower neighbour do not hold
+            // each other's next points, so they load them too
             for (size_t r = 0; r < rds.size(); ++r) {
                 const Rd &R = rds[r];
                 const std::string yz = "y + (" + std::to_string(R.dy) + "), z + (" + std::to_string(R.dz) + ")";
@@ -594,7 +592,7 @@ void generate(dcp_fused *p) {
                     continue;
                 }
                 if (R.dx != 0) {
-                    const std::string ne = R.dx < 0 ? "lane == 0" : "lane == 63 || x + 2 * V > nx";
+                    const std::string ne = R.dx < 0 ? "lane == 0 || rg" : "lane == 63 || x0 + 2 * V > nx";
                     b << "            const bool ne" << r << " = " << ne << ";\n";
                     for (int j = 0; j < V; ++j) {
                         const int e = j + R.dx;
@@ -613,24 +611,19 @@ void generate(dcp_fused *p) {
                     }
                     b << "            }\n";
                 }
-                b << "            " << T << " g" << r << "[V];\n"
-                  << "#pragma unroll\n"
-                  << "            for (int j = 0; j < V; ++j) g" << r << "[j] = " << T << "(0);\n"
-                  << "            if (mrg != 0 && rg) dcp_fixel<" << T << ", I>(m" << R.field << ", g" << r << ", x, (I)("
-                  << R.dx << "), " << yz << ", nx, ny, nz, bc);\n";
             }
             // the next plane's top slot of every group, on every path (loads
             // complete in order: the per-point loads above go out first, so
             // waiting for them does not wait for these)
             for (size_t g = 0; g < grps.size(); ++g)
                 b << "            const bool WP" << g << " = " << slot_fn(g) << "(m" << grps[g].field << ", P" << g
-                  << ", xc, y + (" << grps[g].dy << "), z + (" << grps[g].dzhi + 1 << "), nx, ny, nz, bc);\n";
+                  << ", x, y + (" << grps[g].dy << "), z + (" << grps[g].dzhi + 1 << "), nx, ny, nz, bc);\n";
             // each read from its slot: element j is element j + dx of this
-            // lane's vector, or of the lower / upper lane's.  In a wave with no
-            // ragged lane whose slots all read as data (every periodic plane,
-            // and every interior one) only the row-end elements need a choice.
+            // lane's vector, or of the lower / upper lane's.  In a wave whose
+            // slots all read as data (every periodic plane, and every interior
+            // one) only the row-end elements need a choice.
             for (size_t r = 0; r < rds.size(); ++r) b << "            " << T << " " << rds[r].dst << "[V];\n";
-            std::string allw = "mrg == 0";
+            std::string allw = "true";
             for (size_t g = 0; g < grps.size(); ++g) {
                 const int span = grps[g].dzhi - grps[g].dzlo + 1;
                 for (int q = 0; q < span; ++q) allw += " && W" + std::to_string(g) + "_" + std::to_string(q);
@@ -664,7 +657,6 @@ void generate(dcp_fused *p) {
                         std::string c = general ? "(" + valid + " ? " + src + " : " + T + "(0))" : src;
                         if (e < 0 || e >= V)
                             c = "dcp_sel(mne, e" + std::to_string(r) + "_" + std::to_string(j) + ", " + c + ")";
-                        if (general) c = "dcp_sel(mrg, g" + std::to_string(r) + "[" + std::to_string(j) + "], " + c + ")";
                         b << "                    " << R.dst << "[" << j << "] = " << c << ";\n";
                     }
                     b << "                }\n";
@@ -709,8 +701,15 @@ void generate(dcp_fused *p) {
               << "        const I xt = L % tiles_x, t = L / tiles_x, y = (t % nyb) * " << kRows
               << " + wv, zb = (t / nyb) * (I)zr;\n"
               << "        if (y >= ny) continue;\n"
-              << "        const I x = xt * " << 64 * V << " + lane * V;\n"
-              << "        if (x >= nx) continue;\n"
+              << "        const I x0 = xt * " << 64 * V << " + lane * V;\n"
+              << "        if (x0 >= nx) continue;\n"
+              // the last lane of a ragged row starts early enough to end with
+              // it; it and the lane before compute the same values for the
+              // points they share  (fetching that lane's points one by
+              // one cost its whole wave: 1001 x 300 x 400 step, FP32 713 -> 324 us,
+              // FP64 800 -> 687)
+              << "        const bool rg = x0 + V > nx;\n"
+              << "        const I x = fast && rg ? nx - V : x0;\n"
               << "        const I ze = (zb + (I)zr < nz ? zb + (I)zr : nz);\n"
               << "        I i = x + nx * y + plane * zb;\n"
               << "        if (!fast) {\n"
@@ -718,7 +717,6 @@ void generate(dcp_fused *p) {
               << "                " << K.fname << "_slow<I>(" << params_pass.str() << ", x, y, z, i, nx, ny, nz);\n"
               << "            continue;\n"
               << "        }\n"
-              << "        const I xc = x + V <= nx ? x : nx - V;\n"
               << b.str() << "    }\n"
               << "}\n";
         }

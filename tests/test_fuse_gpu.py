@@ -241,6 +241,27 @@ def test_large_and_long_shifts_bitwise(shape, bc, dtype):
             assert np.array_equal(g, w), (shape, bc, dtype, fuse)
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("nx", [
+    15,              # a wave's only row end, every remainder of whole vectors below
+    127, 129, 131,   # one point short of and past a float64 x tile of 128 points
+    254, 255, 257, 258, 259,  # the same for float32 tiles of 256, each remainder
+])
+def test_ragged_row_ends_bitwise(nx, bc, dtype):
+    P = shifts_program(dtype)
+    dt = np.float64 if dtype == "f64" else np.float32
+    r = np.random.default_rng(nx + bc)
+    arrays = [r.uniform(-1, 1, (5, 6, nx)).astype(dt) for _ in range(2)]
+    want = fuse_interp.run(P.text(), arrays, {"p": 0.375}, bc)
+    for fuse in (True, False):
+        prog = P.compile(fuse)
+        say("fuse ragged rows", nx, bc, dtype, fuse)
+        got = run_gpu(prog, arrays, {"p": 0.375}, bc)
+        for g, w in zip(got, want):
+            assert np.array_equal(g, w), (nx, bc, dtype, fuse)
+
+
 def test_grid_beyond_32_bit_indices_sampled():
     # 2048 x 1024 x 1030 float32 points (8.6 GB a field): point indices pass
     # 2^31, so the 64-bit index variant runs; outputs are checked at the
