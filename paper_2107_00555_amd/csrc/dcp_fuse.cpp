@@ -50,7 +50,15 @@
 
 namespace {
 
-constexpr int kRows = 4;  // waves (rows) per workgroup (8 measured slightly slower)
+constexpr int kRows = 4;  // waves per workgroup (8 measured slightly slower)
+// Variants of a kernel: 32-bit and 64-bit indices with one row per lane,
+// 32-bit indices with two rows, which share the planes that both read
+// (512^3 step, us: FP64 619 -> 600, FP32 306 -> 297; adjoint FP64 613 -> 587).
+// The last only where a lane's two rows hold at most kTwoRowVectors vectors (four
+// registers each; the step's hold 24 and its kernel takes 89 registers, five
+// waves per SIMD), so that larger programs keep their waves.
+constexpr const char *kVariants[] = {"_i32", "_i64", "_i32r2"};
+constexpr int kTwoRowVectors = 28;
 
 enum Kind { K_INPUT, K_PARAM, K_CONST, K_ADD, K_SUB, K_MUL, K_DIV, K_NEG, K_COPY, K_SHIFT };
 
@@ -73,6 +81,7 @@ struct Kernel {
     std::vector<int> reads;       // fields read from memory (inputs or stored)
     std::vector<int> writes;      // fields stored here
     std::string fname;
+    bool two = false;             // has the variant with two rows per lane
 };
 
 bool is_ident(const std::string &s) {
@@ -419,6 +428,10 @@ void generate(dcp_fused *p) {
       << "    dcp_ldv<T, NT>(a + (xc + nx * (dcp_wrap<I>(yy, ny) + ny * dcp_wrap<I>(zz, nz))), q);\n"
       << "    return bc != 0 || (dcp_in<I>(yy, ny) && dcp_in<I>(zz, nz));\n"
       << "}\n"
+      << "template <typename T> __device__ __forceinline__ void dcp_zero(bool data, T *q) {\n"
+      << "#pragma unroll\n"
+      << "    for (int j = 0; j < V; ++j) q[j] = data ? q[j] : T(0);\n"
+      << "}\n"
       // V points (x + j + dx, yy, zz) through the boundary rule, one wrap
       // per axis at most; f holds zeros on entry
       << "template <typename T, typename I> __device__ __forceinline__ void dcp_fixel(const T *__restrict__ a, T *f, "
@@ -432,7 +445,7 @@ void generate(dcp_fused *p) {
       << "    }\n"
       << "}\n";
     for (size_t k = 0; k < p->kernels.size(); ++k) {
-        const Kernel &K = p->kernels[k];
+        Kernel &K = p->kernels[k];
         std::ostringstream params_decl, params_pass;
         bool first = true;
         auto sep = [&]() {
@@ -461,7 +474,7 @@ void generate(dcp_fused *p) {
         params_decl << "i64 nx_, i64 ny_, i64 nz_, int bc";
         params_pass << "nx_, ny_, nz_, bc";
 
-        // the kernel's memory reads (program order) and their groups
+        // the kernel's memory reads (program order)
         struct Rd {
             std::string dst;
             int field, dx, dy, dz, grp;
@@ -470,43 +483,28 @@ void generate(dcp_fused *p) {
             int field, dy, dzlo, dzhi;
         };
         std::vector<Rd> rds;
-        std::vector<Grp> grps;
         std::vector<char> loaded(p->nodes.size(), 0);
-        auto add_read = [&](const std::string &dst, int field, int dx, int dy, int dz) {
-            int g = -1;
-            for (size_t q = 0; q < grps.size(); ++q)
-                if (grps[q].field == field && grps[q].dy == dy) g = (int)q;
-            if (g < 0) {
-                grps.push_back(Grp{field, dy, dz, dz});
-                g = (int)grps.size() - 1;
-            }
-            grps[g].dzlo = std::min(grps[g].dzlo, dz);
-            grps[g].dzhi = std::max(grps[g].dzhi, dz);
-            rds.push_back(Rd{dst, field, dx, dy, dz, g});
-        };
         for (int i : K.nodes) {
             const Node &n = p->nodes[i];
             if (n.kind == K_SHIFT) {
-                add_read("v" + std::to_string(i), n.a, n.dx, n.dy, n.dz);
+                rds.push_back(Rd{"v" + std::to_string(i), n.a, n.dx, n.dy, n.dz, -1});
                 continue;
             }
             for (int o : {n.a, n.b}) {
                 if (o < 0) continue;
                 const Node &m = p->nodes[o];
                 if (!m.field || loaded[o] || !(m.kind == K_INPUT || m.kernel != (int)k)) continue;
-                add_read("r" + std::to_string(o), o, 0, 0, 0);
+                rds.push_back(Rd{"r" + std::to_string(o), o, 0, 0, 0, -1});
                 loaded[o] = 1;
             }
         }
-        // a group streams (non-temporal loads) when every read of its field
-        // in this kernel is unshifted: no other tile or plane needs its lines
-        std::vector<char> streamed(grps.size(), 1);
-        for (const Rd &r : rds)
-            if (r.dx != 0 || r.dy != 0 || r.dz != 0)
-                for (size_t g = 0; g < grps.size(); ++g)
-                    if (grps[g].field == r.field) streamed[g] = 0;
-        auto slot_fn = [&](size_t g) -> std::string {
-            return std::string("dcp_slot<") + T + ", I" + (streamed[g] ? ", true" : "") + ">";
+        // a field streams (non-temporal loads) when every read of it in this
+        // kernel is unshifted: no other tile or plane needs its lines
+        auto slot_fn = [&](int field) -> std::string {
+            bool streamed = true;
+            for (const Rd &r : rds)
+                if (r.field == field && (r.dx != 0 || r.dy != 0 || r.dz != 0)) streamed = false;
+            return std::string("dcp_slot<") + T + ", I" + (streamed ? ", true" : "") + ">";
         };
         int maxd[3] = {0, 0, 0};
         for (const Rd &r : rds) {
@@ -562,17 +560,42 @@ void generate(dcp_fused *p) {
         s << "    " << K.fname << "_comp<I>(" << params_pass.str() << ", i, x, nx" << rd_pass.str() << ");\n"
           << "}\n";
 
-        for (const char *suffix : {"_i32", "_i64"}) {
+        const std::vector<Rd> one = rds;
+        for (const char *suffix : kVariants) {
             const char *I = suffix[2] == '3' ? "int" : "i64";
+            const int rows = suffix[4] == 'r' ? 2 : 1;  // rows of a lane
+            // every row's reads, and their groups: the reads of one field at
+            // one y share a queue over z
+            std::vector<Rd> rds;
+            std::vector<Grp> grps;
+            for (int y = 0; y < rows; ++y)
+                for (const Rd &o : one) {
+                    const int dy = o.dy + y;
+                    int g = 0;
+                    while (g < (int)grps.size() && !(grps[g].field == o.field && grps[g].dy == dy)) ++g;
+                    if (g == (int)grps.size()) grps.push_back(Grp{o.field, dy, o.dz, o.dz});
+                    grps[g].dzlo = std::min(grps[g].dzlo, o.dz);
+                    grps[g].dzhi = std::max(grps[g].dzhi, o.dz);
+                    rds.push_back(Rd{y ? o.dst + "_1" : o.dst, o.field, o.dx, dy, o.dz, g});
+                }
+            if (rows == 2) {  // queue slots and the next plane's, shifted reads and their row-end values
+                int held = 0;
+                for (const Grp &g : grps) held += g.dzhi - g.dzlo + 2;
+                for (const Rd &r : rds) held += r.dx == 0 ? 0 : std::abs(r.dx) > V ? 1 : 2;
+                K.two = held <= kTwoRowVectors;
+                if (!K.two) continue;
+            }
             std::ostringstream b;  // the fast path's per-tile code
             // queue slots: Q<g>_<k> holds plane z + dzlo + k; P<g> the next top
             for (size_t g = 0; g < grps.size(); ++g) {
                 const int span = grps[g].dzhi - grps[g].dzlo + 1;
                 for (int q = 0; q < span; ++q)
                     b << "        " << T << " Q" << g << "_" << q << "[V];\n"
-                      << "        bool W" << g << "_" << q << " = " << slot_fn(g) << "(m" << grps[g].field << ", Q"
+                      << "        bool W" << g << "_" << q << " = " << slot_fn(grps[g].field) << "(m" << grps[g].field << ", Q"
                       << g << "_" << q << ", x, y + (" << grps[g].dy << "), zb + (" << grps[g].dzlo + q
                       << "), nx, ny, nz, bc);\n";
+                for (int q = 0; q + 1 < span; ++q)
+                    b << "        dcp_zero<" << T << ">(W" << g << "_" << q << ", Q" << g << "_" << q << ");\n";
                 b << "        " << T << " P" << g << "[V];\n";
             }
             b << "        for (I z = zb; z < ze; ++z, i += plane) {\n";
@@ -616,63 +639,60 @@ void generate(dcp_fused *p) {
             // complete in order: the per-point loads above go out first, so
             // waiting for them does not wait for these)
             for (size_t g = 0; g < grps.size(); ++g)
-                b << "            const bool WP" << g << " = " << slot_fn(g) << "(m" << grps[g].field << ", P" << g
+                b << "            const bool WP" << g << " = " << slot_fn(grps[g].field) << "(m" << grps[g].field << ", P" << g
                   << ", x, y + (" << grps[g].dy << "), z + (" << grps[g].dzhi + 1 << "), nx, ny, nz, bc);\n";
-            // each read from its slot: element j is element j + dx of this
-            // lane's vector, or of the lower / upper lane's.  In a wave whose
-            // slots all read as data (every periodic plane, and every interior
-            // one) only the row-end elements need a choice.
-            for (size_t r = 0; r < rds.size(); ++r) b << "            " << T << " " << rds[r].dst << "[V];\n";
-            std::string allw = "true";
+            // a top slot outside the grid reads as zero (a uniform choice,
+            // made once per slot: the queue passes the zeros down)
             for (size_t g = 0; g < grps.size(); ++g) {
-                const int span = grps[g].dzhi - grps[g].dzlo + 1;
-                for (int q = 0; q < span; ++q) allw += " && W" + std::to_string(g) + "_" + std::to_string(q);
+                const std::string top = std::to_string(g) + "_" + std::to_string(grps[g].dzhi - grps[g].dzlo);
+                b << "            dcp_zero<" << T << ">(W" << top << ", Q" << top << ");\n";
             }
-            for (int general = 0; general < 2; ++general) {
-                b << (general ? "            } else {\n" : "            if (" + allw + ") {\n");
-                for (size_t r = 0; r < rds.size(); ++r) {
-                    const Rd &R = rds[r];
-                    const std::string slot =
-                        "Q" + std::to_string(R.grp) + "_" + std::to_string(R.dz - grps[R.grp].dzlo);
-                    const std::string valid =
-                        "W" + std::to_string(R.grp) + "_" + std::to_string(R.dz - grps[R.grp].dzlo);
-                    if (std::abs(R.dx) > V) {
-                        b << "#pragma unroll\n"
-                          << "                for (int j = 0; j < V; ++j) " << R.dst << "[j] = f" << r << "[j];\n";
-                        continue;
-                    }
-                    b << "                {\n";
-                    if (R.dx != 0)
-                        b << "                    const unsigned long long mne = __builtin_amdgcn_ballot_w64(ne" << r
-                          << ");\n";
-                    for (int j = 0; j < V; ++j) {
-                        const int e = j + R.dx;
-                        std::string src;
-                        if (e < 0)
-                            src = "dcp_dpp<DCP_LOWER>(" + slot + "[" + std::to_string(e + V) + "])";
-                        else if (e >= V)
-                            src = "dcp_dpp<DCP_UPPER>(" + slot + "[" + std::to_string(e - V) + "])";
-                        else
-                            src = slot + "[" + std::to_string(e) + "]";
-                        std::string c = general ? "(" + valid + " ? " + src + " : " + T + "(0))" : src;
-                        if (e < 0 || e >= V)
-                            c = "dcp_sel(mne, e" + std::to_string(r) + "_" + std::to_string(j) + ", " + c + ")";
-                        b << "                    " << R.dst << "[" << j << "] = " << c << ";\n";
-                    }
-                    b << "                }\n";
+            // each read from its slot: element j is element j + dx of this
+            // lane's vector, or of the lower / upper lane's; the row-end
+            // elements are a choice
+            for (size_t r = 0; r < rds.size(); ++r) {
+                const Rd &R = rds[r];
+                const std::string slot =
+                    "Q" + std::to_string(R.grp) + "_" + std::to_string(R.dz - grps[R.grp].dzlo);
+                if (std::abs(R.dx) > V) {
+                    b << "            const " << T << " *" << R.dst << " = f" << r << ";\n";
+                    continue;
                 }
+                if (R.dx == 0) {
+                    b << "            const " << T << " *" << R.dst << " = " << slot << ";\n";
+                    continue;
+                }
+                b << "            " << T << " " << R.dst << "[V];\n"
+                  << "            {\n"
+                  << "                const unsigned long long mne = __builtin_amdgcn_ballot_w64(ne" << r << ");\n";
+                for (int j = 0; j < V; ++j) {
+                    const int e = j + R.dx;
+                    std::string c;
+                    if (e < 0)
+                        c = "dcp_dpp<DCP_LOWER>(" + slot + "[" + std::to_string(e + V) + "])";
+                    else if (e >= V)
+                        c = "dcp_dpp<DCP_UPPER>(" + slot + "[" + std::to_string(e - V) + "])";
+                    else
+                        c = slot + "[" + std::to_string(e) + "]";
+                    if (e < 0 || e >= V)
+                        c = "dcp_sel(mne, e" + std::to_string(r) + "_" + std::to_string(j) + ", " + c + ")";
+                    b << "                " << R.dst << "[" << j << "] = " << c << ";\n";
+                }
+                b << "            }\n";
             }
-            b << "            }\n";
-            b << "            " << K.fname << "_comp<I>(" << params_pass.str() << ", i, x, nx" << rd_pass.str()
-              << ");\n";
+            for (int y = 0; y < rows; ++y) {
+                b << "            " << (y ? "if (y + 1 < ny) " : "") << K.fname << "_comp<I>(" << params_pass.str()
+                  << (y ? ", i + nx" : ", i") << ", x, nx";
+                for (size_t r = 0; r < one.size(); ++r) b << ", " << rds[y * one.size() + r].dst;
+                b << ");\n";
+            }
             // the queues move up one plane
             for (size_t g = 0; g < grps.size(); ++g) {
                 const int span = grps[g].dzhi - grps[g].dzlo + 1;
                 for (int q = 0; q + 1 < span; ++q)
                     b << "#pragma unroll\n"
                       << "            for (int j = 0; j < V; ++j) Q" << g << "_" << q << "[j] = Q" << g << "_" << q + 1
-                      << "[j];\n"
-                      << "            W" << g << "_" << q << " = W" << g << "_" << q + 1 << ";\n";
+                      << "[j];\n";
                 b << "#pragma unroll\n"
                   << "            for (int j = 0; j < V; ++j) Q" << g << "_" << span - 1 << "[j] = P" << g << "[j];\n"
                   << "            W" << g << "_" << span - 1 << " = WP" << g << ";\n";
@@ -683,7 +703,7 @@ void generate(dcp_fused *p) {
               << params_decl.str() << ", int zr, i64 tiles_x_, i64 nchunk_) {\n"
               << "    typedef " << I << " I;\n"
               << "    const I nx = (I)nx_, ny = (I)ny_, nz = (I)nz_, tiles_x = (I)tiles_x_;\n"
-              << "    const I nyb = (ny + " << kRows - 1 << ") / " << kRows << ", nwg = tiles_x * nyb * (I)nchunk_;\n"
+              << "    const I nyb = (ny + " << kRows * rows - 1 << ") / " << kRows * rows << ", nwg = tiles_x * nyb * (I)nchunk_;\n"
               << "    const I G = (I)gridDim.x, bk = (I)blockIdx.x;\n"
               // workgroups go to the 8 XCDs in turn: give each XCD one
               // contiguous range of tiles so row neighbours share its L2
@@ -698,8 +718,8 @@ void generate(dcp_fused *p) {
               // a workgroup's four waves take four consecutive rows of one x
               // tile, so a wave's y-neighbour rows are its siblings' rows
               << "    for (I L = lb; L < nwg; L += G) {\n"
-              << "        const I xt = L % tiles_x, t = L / tiles_x, y = (t % nyb) * " << kRows
-              << " + wv, zb = (t / nyb) * (I)zr;\n"
+              << "        const I xt = L % tiles_x, t = L / tiles_x, y = ((t % nyb) * " << kRows
+              << " + wv) * " << rows << ", zb = (t / nyb) * (I)zr;\n"
               << "        if (y >= ny) continue;\n"
               << "        const I x0 = xt * " << 64 * V << " + lane * V;\n"
               << "        if (x0 >= nx) continue;\n"
@@ -714,7 +734,9 @@ void generate(dcp_fused *p) {
               << "        I i = x + nx * y + plane * zb;\n"
               << "        if (!fast) {\n"
               << "            for (I z = zb; z < ze; ++z, i += plane)\n"
-              << "                " << K.fname << "_slow<I>(" << params_pass.str() << ", x, y, z, i, nx, ny, nz);\n"
+              << "                for (I r = 0; r < " << rows << " && y + r < ny; ++r)\n"
+              << "                    " << K.fname << "_slow<I>(" << params_pass.str()
+              << ", x, y + r, z, i + r * nx, nx, ny, nz);\n"
               << "            continue;\n"
               << "        }\n"
               << b.str() << "    }\n"
@@ -855,10 +877,14 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
     if (it == p->modules.end()) {
         hipModule_t m;
         if (hipModuleLoadData(&m, p->code.data()) != hipSuccess) return DCP_E_HIP;
-        std::vector<hipFunction_t> fns;  // per kernel: 32-bit, then 64-bit indices
+        std::vector<hipFunction_t> fns;  // per kernel, in the order of kVariants
         for (const Kernel &K : p->kernels) {
-            for (const char *suffix : {"_i32", "_i64"}) {
-                hipFunction_t f;
+            for (const char *suffix : kVariants) {
+                hipFunction_t f = nullptr;
+                if (suffix[4] && !K.two) {
+                    fns.push_back(f);
+                    continue;
+                }
                 if (hipModuleGetFunction(&f, m, (K.fname + suffix).c_str()) != hipSuccess) {
                     hipModuleUnload(m);
                     return DCP_E_HIP;
@@ -877,21 +903,12 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
         return static_cast<char *>(ws) + (size_t)m.buf * align256(fb);
     };
     // wave tiles: 64*V x-points of one row (V points per lane, 16 bytes) over
-    // zr consecutive planes; a workgroup takes one x tile of four consecutive
-    // rows, workgroups ordered x tile, then row block, then plane chunk; a
+    // zr consecutive planes; a workgroup takes one x tile of four (two rows per
+    // lane: eight) consecutive rows, workgroups ordered x tile, then row block, then plane chunk; a
     // one-dimensional grid of at most 2^20 workgroups strides over them.  zr
     // doubles, up to 16, while at least 4096 workgroups (16 per CU) remain.
     const int64_t tile_w = p->dtype == DCP_F64 ? 128 : 256;
     int64_t tiles_x = (nx + tile_w - 1) / tile_w;
-    int64_t zr = 1;
-    while (zr < 16 && tiles_x * ny * ((nz + 2 * zr - 1) / (2 * zr)) >= 4 * 4096) zr *= 2;
-    if (const char *e = dcp::tuning_env("DCP_FUSE_ZR")) {  // tuning override: planes per wave tile
-        const long v = std::strtol(e, nullptr, 10);
-        if (v >= 1 && v <= 4096) zr = v;
-    }
-    int64_t nchunk = (nz + zr - 1) / zr;
-    const unsigned grid = (unsigned)std::min<int64_t>(tiles_x * ((ny + kRows - 1) / kRows) * nchunk, 1 << 20);
-    int zr32 = (int)zr;
     double smax[3] = {0, 0, 0};  // largest |offset| of any shifted read, per axis
     for (const Node &m : p->nodes)
         if (m.kind == K_SHIFT) {
@@ -908,6 +925,20 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     for (size_t k = 0; k < p->kernels.size(); ++k) {
         const Kernel &K = p->kernels[k];
+        // two rows per lane from 16 rows on (every y-neighbour one wrap away);
+        // below, the odd row left over would cost more
+        const bool two = K.two && idx32 && ny >= 16 + smax[1];
+        const int wg_rows = two ? 2 * kRows : kRows;
+        const int64_t yblocks = (ny + wg_rows - 1) / wg_rows;
+        int64_t zr = 1;
+        while (zr < 16 && tiles_x * yblocks * ((nz + 2 * zr - 1) / (2 * zr)) >= 4096) zr *= 2;
+        if (const char *e = dcp::tuning_env("DCP_FUSE_ZR")) {  // tuning override: planes per wave tile
+            const long v = std::strtol(e, nullptr, 10);
+            if (v >= 1 && v <= 4096) zr = v;
+        }
+        int64_t nchunk = (nz + zr - 1) / zr;
+        const unsigned grid = (unsigned)std::min<int64_t>(tiles_x * yblocks * nchunk, 1 << 20);
+        int zr32 = (int)zr;
         std::vector<void *> ptrs;
         for (int r : K.reads) ptrs.push_back(ptr_of(r));
         for (int w : K.writes) ptrs.push_back(ptr_of(w));
@@ -922,7 +953,7 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
         args.push_back(&zr32);
         args.push_back(&tiles_x);
         args.push_back(&nchunk);
-        hipFunction_t fn = fns[2 * k + (idx32 ? 0 : 1)];
+        hipFunction_t fn = fns[3 * k + (two ? 2 : idx32 ? 0 : 1)];
         if (hipModuleLaunchKernel(fn, grid, 1, 1, 64 * kRows, 1, 1, 0, st, args.data(),
                                   nullptr) != hipSuccess)
             return DCP_E_HIP;

@@ -262,6 +262,25 @@ def test_ragged_row_ends_bitwise(nx, bc, dtype):
             assert np.array_equal(g, w), (nx, bc, dtype, fuse)
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("shape", [
+    (131, 16, 5),  # one row per lane: 16 rows plus the largest y offset are needed for two
+    (300, 17, 5),  # two rows per lane, the last lane's second row past the end
+    (259, 24, 5),  # whole workgroups of eight rows
+    (2, 18, 5),    # two rows per lane, every point through the rule
+])
+def test_two_rows_per_lane_bitwise(shape, bc, dtype):
+    P = step_program(dtype)
+    dt = np.float64 if dtype == "f64" else np.float32
+    u0, f = (v.astype(dt) for v in rand_fields(shape, 2000 + sum(shape)))
+    want = fuse_interp.run(P.text(), [u0, f], PARAMS, bc)[0]
+    for fuse in (True, False):
+        say("fuse two rows", shape, bc, dtype, fuse)
+        (got,) = run_gpu(P.compile(fuse), [u0, f], PARAMS, bc)
+        assert np.array_equal(got, want), (shape, bc, dtype, fuse)
+
+
 def test_grid_beyond_32_bit_indices_sampled():
     # 2048 x 1024 x 1030 float32 points (8.6 GB a field): point indices pass
     # 2^31, so the 64-bit index variant runs; outputs are checked at the
