@@ -7,6 +7,7 @@ scratch memory comes from torch's allocator as a uint8 workspace tensor.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 
 import torch
@@ -20,9 +21,12 @@ __all__ = ["Coeffs", "DcpError", "DIRICHLET0", "PERIODIC", "FUSED", "UNFUSED",
            "jacobi_1d", "jacobi_2d", "revolve_forward", "revolve_adjoint"]
 
 
+_BC = {"dirichlet0": DIRICHLET0, "dirichlet": DIRICHLET0, "periodic": PERIODIC}
+
+
 def bc_code(bc) -> int:
     if isinstance(bc, str):
-        return {"dirichlet0": DIRICHLET0, "dirichlet": DIRICHLET0, "periodic": PERIODIC}[bc.lower()]
+        return _BC[bc.lower()]
     return int(bc)
 
 
@@ -43,7 +47,7 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _field(name: str, t: torch.Tensor, like: torch.Tensor | None = None) -> torch.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor (got device {t.device})")
     if t.dim() != 3:
         raise ValueError(f"{name} must be 3-D shaped (nz, ny, nx), got {tuple(t.shape)}")
@@ -56,11 +60,22 @@ def _field(name: str, t: torch.Tensor, like: torch.Tensor | None = None) -> torc
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# A small grid's step spends longer in this binding than on the GPU, so the
+# device is switched only where it is not the current one, and the stream's
+# handle is read without making a Stream object of it (together with plain
+# integer pointers: a 64^3 step with norms 19.3 -> 15.6 us).
+_HERE = contextlib.nullcontext()
+
+
+def _on(device: torch.device):
+    return _HERE if torch.cuda.current_device() == device.index else torch.cuda.device(device)
+
+
+def _stream(device: torch.device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def workspace(nbytes: int, device) -> torch.Tensor | None:
@@ -123,7 +138,7 @@ def step(u: torch.Tensor, f: torch.Tensor, coeffs, bc, impl="fused", norms: bool
     ws = workspace(wsb, u.device)
     n2 = torch.empty(2, dtype=torch.float64, device=u.device) if norms else None
     fn = _lib.lib().dcp_step_fused if ic == FUSED else _lib.lib().dcp_step_unfused
-    with torch.cuda.device(u.device):
+    with _on(u.device):
         _lib.check(fn.__name__, fn(dt, _ptr(u), _ptr(f), _ptr(out), nx, ny, nz, ctypes.byref(c),
                                    bc_code(bc), _ptr(n2), _ptr(ws), wsb, _stream(u.device)))
     return out, n2
@@ -146,7 +161,7 @@ def step_noalloc(u: torch.Tensor, f: torch.Tensor, coeffs, bc, out: torch.Tensor
     dt = _dtype_code(u)
     nz, ny, nx = u.shape
     c = Coeffs.make(coeffs)
-    with torch.cuda.device(u.device):
+    with _on(u.device):
         _lib.check("dcp_step_fused_noalloc", _lib.lib().dcp_step_fused_noalloc(
             dt, _ptr(u), _ptr(f), _ptr(out), nx, ny, nz, ctypes.byref(c), bc_code(bc), _ptr(norms2),
             _stream(u.device)))
@@ -176,7 +191,7 @@ def run(u: torch.Tensor, f: torch.Tensor, coeffs, T: int, bc, impl="fused", tblo
         check_ckpt(ckpt, T, ckpt_every, u)
     elif ckpt_every:
         ckpt = torch.empty((num_slots(T, ckpt_every), nz, ny, nx), dtype=u.dtype, device=u.device)
-    with torch.cuda.device(u.device):
+    with _on(u.device):
         _lib.check("dcp_run", _lib.lib().dcp_run(
             dt, ic, _ptr(u), _ptr(f), nx, ny, nz, ctypes.byref(c), bc_code(bc), int(T), int(tblock),
             _ptr(energy), _ptr(resid), _ptr(ckpt), int(ckpt_every), _ptr(ws), wsb, _stream(u.device)))
@@ -208,7 +223,7 @@ def adjoint_run(ckpt: torch.Tensor | None, ckpt_every: int, f: torch.Tensor, lam
     gab = torch.empty(2, dtype=torch.float64, device=lam_T.device)
     gf = torch.empty_like(lam_T) if want_f else None
     gg = torch.empty(1, dtype=torch.float64, device=lam_T.device) if want_gamma else None
-    with torch.cuda.device(lam_T.device):
+    with _on(lam_T.device):
         _lib.check("dcp_adjoint_run", _lib.lib().dcp_adjoint_run(
             dt, _ptr(ckpt), int(ckpt_every), _ptr(f), _ptr(lam_T), nx, ny, nz, ctypes.byref(c),
             bc_code(bc), int(T), int(tblock), _ptr(grad_u0), _ptr(gab), _ptr(gf), _ptr(gg), _ptr(ws), wsb,
@@ -234,7 +249,7 @@ def revolve_forward(u: torch.Tensor, f: torch.Tensor, coeffs, T: int, bc, nslots
     c = Coeffs.make(coeffs)
     wsb = _lib.revolve_workspace_bytes(dt, nx, ny, nz, T, nslots, reserve_sum)
     ws = workspace(wsb, u.device)
-    with torch.cuda.device(u.device):
+    with _on(u.device):
         _lib.check("dcp_revolve_forward", _lib.lib().dcp_revolve_forward(
             dt, _ptr(u), _ptr(f), nx, ny, nz, ctypes.byref(c), bc_code(bc), int(T), int(nslots), int(tblock),
             _ptr(ws), wsb, _stream(u.device)))
@@ -259,7 +274,7 @@ def revolve_adjoint(ws: torch.Tensor, f: torch.Tensor, lam_T: torch.Tensor, coef
     gab = torch.empty(2, dtype=torch.float64, device=lam_T.device)
     gf = torch.empty_like(lam_T) if want_f else None
     gg = torch.empty(1, dtype=torch.float64, device=lam_T.device) if want_gamma else None
-    with torch.cuda.device(lam_T.device):
+    with _on(lam_T.device):
         _lib.check("dcp_revolve_adjoint", _lib.lib().dcp_revolve_adjoint(
             dt, _ptr(f), _ptr(lam_T), nx, ny, nz, ctypes.byref(c), bc_code(bc), int(T), int(nslots), int(tblock),
             _ptr(grad_u0), _ptr(gab), _ptr(gf), _ptr(gg), _ptr(ws) if ws.numel() else None, ws.numel(),
@@ -296,7 +311,7 @@ def jacobi_1d(A: torch.Tensor, B: torch.Tensor, tsteps: int, tblock: int = 0,
     n = A.shape[0]
     wsb = _lib.jacobi_workspace_bytes(1, n, 1, tsteps, tblock)
     ws = _ws(ws, wsb, A.device)
-    with torch.cuda.device(A.device):
+    with _on(A.device):
         _lib.check("dcp_jacobi_1d", _lib.lib().dcp_jacobi_1d(
             int(tsteps), _ptr(A), _ptr(B), n, int(tblock), _ptr(ws), wsb, _stream(A.device)))
     return A, B
@@ -309,7 +324,7 @@ def jacobi_2d(A: torch.Tensor, B: torch.Tensor, tsteps: int, tblock: int = 0,
     n0, n1 = A.shape
     wsb = _lib.jacobi_workspace_bytes(2, n0, n1, tsteps, tblock)
     ws = _ws(ws, wsb, A.device)
-    with torch.cuda.device(A.device):
+    with _on(A.device):
         _lib.check("dcp_jacobi_2d", _lib.lib().dcp_jacobi_2d(
             int(tsteps), _ptr(A), _ptr(B), n0, n1, int(tblock), _ptr(ws), wsb, _stream(A.device)))
     return A, B

@@ -260,7 +260,7 @@ bool blk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, size_t lds_l
     for (int bz : {4, 8}) {
         const int64_t nbz = (nz + bz - 1) / bz;
         if (nbz > 256) continue;
-        for (int64_t nbx = 1; nbx <= 256 && nbx <= nx; ++nbx) {
+        for (int64_t nbx = 1; nbx * nbz <= 256 && nbx <= nx; ++nbx) {
             const int64_t bx = (nx + nbx - 1) / nbx, fx = bx + 2 * B;
             int64_t by = kLanes / fx - 2 * B;
             if (by < 1) continue;

@@ -890,20 +890,24 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
         const size_t lds = (size_t)tbk_lds_rows(B, ty, ln.ring) * (size_t)chf * 16;
         if (lds > lds_limit) return;
         if (lds < (size_t)(ln.nt / 64) * 2 * B * sizeof(double)) return;
-        const int64_t nslab = (ny + ty - 1) / ty;
+        const int32_t nslab = ((int32_t)ny + ty - 1) / ty;
         if (nslab * nseg > 65536) return;
-        const int64_t cols = nslab * nseg;
-        int64_t runs = 256 / cols;
-        if (runs < 1) runs = 1;
-        if (runs > nz) runs = nz;
-        const int64_t zc = (nz + runs - 1) / runs;
-        runs = (nz + zc - 1) / zc;
+        const int32_t cols = (int32_t)(nslab * nseg);
         // time of a pass: rounds of 256 workgroups, planes of a z-run with the
         // 2(B-1) that fill and drain its pipeline and about three for the
         // prologue, and a plane's time, about half of which depends on the
         // frame's size
         const double plane = 1.0 + (double)(r0 * chf) / (double)(ln.nt * ln.km);
-        const double cost = (double)((cols * runs + 255) / 256) * (double)(zc + 2 * (B - 1) + 3) * plane;
+        // (rounds and a run's planes cover cols * nz planes between them, so most
+        // tiles are refused here, before the divisions: with the heights bounded
+        // below, planning a run of 512^3 79 -> 33 us, of 64^3 23 -> 11 us)
+        if (((double)cols * (double)nz / 256.0 + 2 * (B - 1) + 3) * plane >= best) return;
+        int32_t runs = 256 / cols;
+        if (runs < 1) runs = 1;
+        if (runs > nz) runs = (int32_t)nz;
+        const int32_t zc = ((int32_t)nz + runs - 1) / runs;
+        runs = ((int32_t)nz + zc - 1) / zc;
+        const double cost = (double)(((int64_t)cols * runs + 255) / 256) * (double)(zc + 2 * (B - 1) + 3) * plane;
         if (cost >= best * (1 - 1e-9)) return;
         best = cost;
         found = true;
@@ -921,7 +925,7 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
         t->nslab = (int)nslab;
         t->zc = (int)zc;
         t->nruns = (int)runs;
-        t->nblk = (int)(cols * runs);
+        t->nblk = (int)((int64_t)cols * runs);
         t->lds_bytes = lds;
         // the 256 workgroups go round-robin to the 8 XCDs and are
         // renumbered so each XCD holds a contiguous run of tiles:
@@ -950,7 +954,9 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
     for (int64_t nseg = 1; nseg <= ch; ++nseg) {
         const int64_t wc = (ch + nseg - 1) / nseg;
         if (nseg > 1 && wc < (shift ? 4 : 8)) break;
-        for (int ty = 24; ty >= 2; --ty) consider(wc, ty);
+        // (only the heights whose frame the lanes hold)
+        const int64_t fit = (int64_t)ln.nt * ln.km / (nseg > 1 ? wc + 2 * halo : ch) - 2 * B;
+        for (int ty = (int)(fit < 24 ? fit : 24); ty >= 2; --ty) consider(wc, ty);
     }
     return found;
 }

@@ -209,7 +209,7 @@ class Fused:
         outputs: tensors like the inputs (allocated when None); ws: a byte
         workspace (allocated when None or too small).  Runs on the inputs'
         device and its current stream.  Returns the list of output tensors."""
-        from .api import bc_code
+        from .api import _on, _stream, bc_code
         if len(inputs) != self.n_inputs or self.n_inputs == 0:
             raise ValueError(f"expected {self.n_inputs} inputs")
         dev = inputs[0].device
@@ -244,9 +244,8 @@ class Fused:
         op = (ctypes.c_void_p * len(outputs))(*[t.data_ptr() for t in outputs])
         pp = (ctypes.c_double * max(1, len(params)))(*[float(v) for v in params])
         nz, ny, nx = shape
-        with torch.cuda.device(dev):
-            stream = ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+        with _on(dev):
             _lib.check("dcp_fuse_run", _load().dcp_fuse_run(
                 self._h, ip, pp, op, nx, ny, nz, bc_code(bc),
-                ctypes.c_void_p(ws.data_ptr()) if wsb else None, wsb, stream))
+                ws.data_ptr() if wsb else None, wsb, _stream(dev)))
         return outputs
