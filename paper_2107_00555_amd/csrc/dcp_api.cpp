@@ -89,6 +89,10 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
     return t;
 }
 
+// Most workgroups of a step whose sums are reduced (a run's workspace holds
+// every step's pairs), and of one without.
+constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
+
 // Tile of the one-step kernels.  Two rows per lane (shape 1) and short z-runs:
 // 8 planes, fewer where that leaves under 1200 workgroups (FP32: 900), down
 // to 2, and to 1 under 512; the planes a run shares with the next come from the XCD's L2,
@@ -98,9 +102,18 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
 // 39.5 / 48.2, 256^3 74 / 79, 512^3 559 / 592; FP32 128^3 8.8 / 17.5, 512^3
 // 280 / 288.  `most` bounds the workgroups (their partial sums): past it the
 // tile takes four rows per lane, then longer runs, up to 64 planes.
+// forward: a forward step (the adjoint bodies need the registers) keeps four
+// rows per lane where that still gives 1500 workgroups, in runs of 4 planes
+// when it has no norms (each run's pair of sums costs there) and, with norms, of
+// 7 (FP32: 6) where 8 would leave the last run short.  us with two rows in runs
+// of 8 and now, with norms: FP32 512^3 291 / 285, 640 x 500 x 300 231 / 218, FP64
+// 640 x 500 x 300 481 / 437, 896 x 279 x 242 301 / 280, 1001 x 400 x 300 644 /
+// 607; without: FP32 512^3 278 / 269, 320^3 87 / 84, 640 x 500 x 300 221 / 202,
+// FP64 the same 463 / 407, 896 x 279 x 242 290 / 258, 512^3 554 / 557.  With 1024
+// workgroups two rows are as fast or faster (256^3 FP64 67.3 / 69.3).
 // DCP_TILE_SHAPE / DCP_TILE_ZC override the choice in tuning runs (with
 // DCP_TUNING=1).
-Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
+Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most, bool forward = false) {
     const int wide = dtype == DCP_F64 ? 2 : 4;
     const int vec = vec_ok ? wide : 1;
     int shape = env_int("DCP_TILE_SHAPE", -1);
@@ -116,6 +129,15 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
         while (zc > 2 && blocks(zc) < (dtype == DCP_F64 ? 1200 : 900)) zc /= 2;
         if (zc == 2 && blocks(2) < 512) zc = 1;
         if (!forced && blocks(zc) > most) shape = 0;
+        if (forward && !forced) {
+            const int narrow = shape;
+            shape = 0;
+            if (blocks(8) < 1500) shape = narrow;
+            else if (most > kSumBlocks) zc = 4;
+            else if (g.nz % 8 != 0) zc = dtype == DCP_F64 ? 7 : 6;
+            else zc = 8;
+            if (shape == 0 && zc < 8 && blocks(zc) > most) zc = 8;
+        }
         while (zc < 64 && blocks(zc) > most) zc *= 2;
     }
     if (g.nz > 0 && zc > g.nz) zc = (int)g.nz;
@@ -123,17 +145,18 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most) {
     return make_tile(g, vec, shape, zc);
 }
 
-// Most workgroups of a step whose sums are reduced (a run's workspace holds
-// every step's pairs), and of one without.
-constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
-
-// Largest workgroup count over both vector widths (workspace sizing must not
+// Largest workgroup count over both vector widths and both kinds of step (workspace sizing must not
 // depend on pointer alignment).
 int max_blocks(int dtype, const Geo &g, int most) {
     if (g.n == 0) return 0;
-    const Tile a = pick_tile(dtype, g, true, most), b = pick_tile(dtype, g, false, most);
-    if (a.nblk < 0 || b.nblk < 0) return -1;
-    return a.nblk > b.nblk ? a.nblk : b.nblk;
+    int nb = 0;
+    for (const bool vec : {true, false})
+        for (const bool forward : {true, false}) {
+            const Tile t = pick_tile(dtype, g, vec, most, forward);
+            if (t.nblk < 0) return -1;
+            if (t.nblk > nb) nb = t.nblk;
+        }
+    return nb;
 }
 
 // ---------------------------------------------------------- workspace layout
@@ -602,7 +625,7 @@ int step_common(int impl, int dtype, const void *u, const void *f, void *u_out, 
     double *partials = norms2 ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
     if (impl == DCP_FUSED) {
         const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}),
-                                norms2 ? kSumBlocks : kPlainBlocks);
+                                norms2 ? kSumBlocks : kPlainBlocks, true);
         DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, u, f, u_out, partials, st));
         if (norms2) DCP_TRY(launch_finalize(partials, t.nblk, t.nblk, 1, norms2, nullptr, 0, st));
     } else {
@@ -870,7 +893,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     const bool vok = vec_ok_for(dtype, g, {u, f, buf, tmp[0], tmp[1], tmp[2], ckpt});
     bool eok = ew_ok({u, f, buf, tmp[0], tmp[1], tmp[2]});  // of every state and temporary
     for (int32_t c = 0; c < nslots; ++c) eok = eok && aligned16(slot(c));
-    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+    const Tile t = pick_tile(dtype, g, vok, kSumBlocks, impl == DCP_FUSED);
     const int nblk_one = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : t.nblk;
     const int stride = w.nblk;  // partial slots per step (>= every kernel's workgroup count)
     double *partials = norms ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
