@@ -115,10 +115,11 @@ constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
 // DCP_TUNING=1).
 Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most, bool forward = false) {
     const int wide = dtype == DCP_F64 ? 2 : 4;
-    const int vec = vec_ok ? wide : 1;
     int shape = env_int("DCP_TILE_SHAPE", -1);
     const bool forced = shape >= 0 && shape < num_shapes();
     if (!forced) shape = 1;
+    // (vectors on ragged rows: compiled for the two shapes chosen here)
+    const int vec = vec_ok && (g.nx % wide == 0 || shape <= 1) ? wide : 1;
     int zc = env_int("DCP_TILE_ZC", 0);
     if (zc <= 0) {
         auto blocks = [&](int z) {

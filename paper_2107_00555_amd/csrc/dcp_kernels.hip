@@ -124,8 +124,16 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return xcd * per + min(xcd, rem) + j;
 }
 
-template <typename T, int VEC, int BXW, int BY, int RY, int BC, int OP, bool RED>
+// RAG: rows that are not a whole number of vectors (nx >= VEC, checked by the
+// host).  A row's last lane starts `sh` points earlier, so that it ends with
+// the row; it and the lane before compute those points alike, and the sums
+// take them from the lane before.  A form of its own: as a run-time value `sh`
+// put two selects per point into every row's sums and took the FP64 forward
+// and adjoint forms with sums from 126 and 128 registers to 130, four waves
+// per SIMD to three.
+template <typename T, int VEC, int BXW, int BY, int RY, int BC, int OP, bool RED, bool RAG>
 __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
+    static_assert(!RAG || VEC > 1, "single elements have no ragged rows");
     constexpr int NW = BXW * BY;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -142,11 +150,7 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
     const int64_t sy = nx, sz = nx * ny;
     const int64_t xt = ((int64_t)tx * (64 * BXW) + wx * 64 + lane) * VEC;
     const bool xok = xt < nx;
-    // a row that is not a whole number of vectors (nx >= VEC, checked by the
-    // host): its last lane starts `sh` points earlier, so that it ends with the
-    // row; it and the lane before compute those points alike, and the sums
-    // take them from the lane before
-    const int sh = VEC > 1 && xok && xt + VEC > nx ? (int)(xt + VEC - nx) : 0;
+    const int sh = RAG && xok && xt + VEC > nx ? (int)(xt + VEC - nx) : 0;
     const int64_t x0 = xt - sh;
     const int64_t yf = ((int64_t)ty * BY + wy) * RY;
     const int nrow = (int)max((int64_t)0, min((int64_t)RY, ny - yf));
@@ -164,16 +168,16 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
     const int64_t ytop = wrap<BC>(yf - 1, ny);
     const int64_t ybot = wrap<BC>(yf + nrow, ny);
     // lanes whose neighbour is not the next lane's first or last point
-    const bool need_l = xok && (lane == 0 || x0 == 0 || sh);
-    const bool need_r = xok && (lane == 63 || xt + 2 * VEC > nx);
+    const bool need_l = xok && (lane == 0 || x0 == 0 || (RAG && sh));
+    const bool need_r = xok && (lane == 63 || (RAG ? xt + 2 * VEC > nx : x0 + VEC >= nx));
     const int64_t xl = wrap<BC>(x0 - 1, nx);
     const int64_t xr = wrap<BC>(x0 + VEC, nx);
 
     const T C0 = (T)a.c0, C1 = (T)a.c1, C2 = (T)a.c2;
     const T C1F = (T)a.c1f, C2F = (T)a.c2f;
 
-    // the value of element e in the sums: 0 where the lane before counts it
-    auto counts = [&](int e, T v) -> double { return e < VEC - 1 && e < sh ? 0.0 : (double)v; };
+    // element e is left out of the sums: the lane before counts it
+    auto twice = [&](int e) -> bool { return RAG && e < VEC - 1 && e < sh; };
 
     // loaders for a resolved plane index zr (-1 = ghost plane) of a stencil
     // operand P (S, or V)
@@ -311,10 +315,10 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                                 acc = fma(-(C1 * c) * c, c, acc);
                                 res[e] = acc;
                                 if constexpr (RED) {
-                                    const double d = counts(e, acc);
-                                    acc0 = fma(d, d, acc0);
-                                    const double dd = d - counts(e, c);
-                                    acc1 = fma(dd, dd, acc1);
+                                    const double d = (double)acc;
+                                    const double dd = d - (double)c;
+                                    acc0 = twice(e) ? acc0 : fma(d, d, acc0);
+                                    acc1 = twice(e) ? acc1 : fma(dd, dd, acc1);
                                 }
                             } else {  // the adjoint ops: c = lambda_{t+1}, qv = u_t
                                 T acc = fma(C0, lapn, c);
@@ -322,8 +326,8 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                                 res[e] = acc;
                                 if constexpr (RED) {
                                     const double du = (double)qv;
-                                    acc0 = fma(counts(e, lapn), du, acc0);
-                                    acc1 = fma(counts(e, c), du * du * du, acc1);
+                                    acc0 = twice(e) ? acc0 : fma((double)lapn, du, acc0);
+                                    acc1 = twice(e) ? acc1 : fma((double)c, du * du * du, acc1);
                                 }
                             }
                         }
@@ -332,7 +336,7 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                     if constexpr (LSUM) {
                         // running sum of the adjoint inputs: lam += lambda_{t+1}
                         T *lp = static_cast<T *>(a.lam) + z * sz + (yf + r) * sy + x0;
-                        if (sh) {  // the lane before adds to the first points
+                        if (RAG && sh) {  // the lane before adds to the first points
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
                                 if (e >= sh) lp[e] = (a.lam_first ? T(0) : lp[e]) + uc[r][e];
@@ -418,12 +422,12 @@ constexpr Shape kShapes[] = {
 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
-template <typename T, int VEC, int BXW, int BY, int RY>
+template <typename T, int VEC, int BXW, int BY, int RY, bool RAG>
 hipError_t launch_shape(int op, int bc, bool reduce, int nblk, const StencilArgs &a,
                         hipStream_t st) {
     const dim3 grid(nblk), block(64 * BXW * BY);
 #define DCP_L(BCV, OPV, REDV) \
-    hipLaunchKernelGGL((stencil_kernel<T, VEC, BXW, BY, RY, BCV, OPV, REDV>), grid, block, 0, st, a)
+    hipLaunchKernelGGL((stencil_kernel<T, VEC, BXW, BY, RY, BCV, OPV, REDV, RAG>), grid, block, 0, st, a)
     if (bc == 0) {
         if (op == SOP_FWD) {
             if (reduce) DCP_L(0, SOP_FWD, true);
@@ -462,12 +466,20 @@ hipError_t launch_shape(int op, int bc, bool reduce, int nblk, const StencilArgs
 template <typename T, int VEC>
 hipError_t launch_vec(int shape, int op, int bc, bool reduce, int nblk, const StencilArgs &a,
                       hipStream_t st) {
+    if constexpr (VEC > 1) {
+        if (a.nx < VEC) return hipErrorInvalidValue;
+        if (a.nx % VEC != 0) {  // the shapes pick_tile gives ragged rows
+            if (shape == 0) return launch_shape<T, VEC, 1, 4, 4, true>(op, bc, reduce, nblk, a, st);
+            if (shape == 1) return launch_shape<T, VEC, 1, 4, 2, true>(op, bc, reduce, nblk, a, st);
+            return hipErrorInvalidValue;
+        }
+    }
     switch (shape) {
-        case 0: return launch_shape<T, VEC, 1, 4, 4>(op, bc, reduce, nblk, a, st);
-        case 1: return launch_shape<T, VEC, 1, 4, 2>(op, bc, reduce, nblk, a, st);
-        case 2: return launch_shape<T, VEC, 2, 2, 4>(op, bc, reduce, nblk, a, st);
-        case 3: return launch_shape<T, VEC, 1, 8, 2>(op, bc, reduce, nblk, a, st);
-        case 4: return launch_shape<T, VEC, 1, 2, 8>(op, bc, reduce, nblk, a, st);
+        case 0: return launch_shape<T, VEC, 1, 4, 4, false>(op, bc, reduce, nblk, a, st);
+        case 1: return launch_shape<T, VEC, 1, 4, 2, false>(op, bc, reduce, nblk, a, st);
+        case 2: return launch_shape<T, VEC, 2, 2, 4, false>(op, bc, reduce, nblk, a, st);
+        case 3: return launch_shape<T, VEC, 1, 8, 2, false>(op, bc, reduce, nblk, a, st);
+        case 4: return launch_shape<T, VEC, 1, 2, 8, false>(op, bc, reduce, nblk, a, st);
         default: return hipErrorInvalidValue;
     }
 }
