@@ -89,75 +89,109 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
     return t;
 }
 
-// Most workgroups of a step whose sums are reduced (a run's workspace holds
-// every step's pairs), and of one without.
+// Most workgroups of a step whose sums are reduced (its pairs of sums are
+// stored), and of one without.
 constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
 
-// Tile of the one-step kernels.  Two rows per lane (shape 1) and short z-runs:
-// 8 planes, fewer where that leaves under 1200 workgroups (FP32: 900), down
-// to 2, and to 1 under 512; the planes a run shares with the next come from the XCD's L2,
-// and the many short workgroups keep every CU busy to the end.  Measured, us
-// per step with norms, against four rows per lane with runs of 8 to 64
-// planes: FP64 64^3 4.9 / 12.2, 96^3 7.8 / 14.1, 128^3 12.8 / 17.9, 192^3
-// 39.5 / 48.2, 256^3 74 / 79, 512^3 559 / 592; FP32 128^3 8.8 / 17.5, 512^3
-// 280 / 288.  `most` bounds the workgroups (their partial sums): past it the
-// tile takes four rows per lane, then longer runs, up to 64 planes.
-// forward: a forward step (the adjoint bodies need the registers) keeps four
-// rows per lane where that still gives 1500 workgroups, in runs of 4 planes
-// when it has no norms (each run's pair of sums costs there) and, with norms, of
-// 7 (FP32: 6) where 8 would leave the last run short.  us with two rows in runs
-// of 8 and now, with norms: FP32 512^3 291 / 285, 640 x 500 x 300 231 / 218, FP64
-// 640 x 500 x 300 481 / 437, 896 x 279 x 242 301 / 280, 1001 x 400 x 300 644 /
-// 607; without: FP32 512^3 278 / 269, 320^3 87 / 84, 640 x 500 x 300 221 / 202,
-// FP64 the same 463 / 407, 896 x 279 x 242 290 / 258, 512^3 554 / 557.  With 1024
-// workgroups two rows are as fast or faster (256^3 FP64 67.3 / 69.3).
+// What a tile's step does: no sums, sums, or the reverse sweep's adjoint step
+// that may recompute its state.
+enum StepUse { kPlainStep, kSumStep, kRecomputeStep };
+
+// Tile of the one-step kernels.  A wave covers 64 vectors of one row; a lane
+// holds two rows (shape 1: 8 rows per workgroup, four waves per SIMD) or four
+// (shape 0: 16 rows, two waves per SIMD, fewer rows read twice), and marches up
+// runs of zc planes, two of which it shares with the next run.  512 workgroups
+// of shape 0 run at once, or 1024 of shape 1.  The rule goes by how many of shape
+// 0 with runs of 8 planes the grid gives; times in us per step (with norms, unless
+// "plain"), the other choice first:
+//   * under 410, four fifths of a round: shape 1, in runs of 8 planes, fewer
+//     where that leaves under 1200 workgroups (FP32: 900), so that every CU has
+//     work: FP64 64^3 12.2 / 4.9, 96^3 14.1 / 7.8, 128^3 20.4 / 16.1;
+//   * up to 512, one round nearly or just full: shape 0, whose runs share less:
+//     FP32 512 x 512 x 64 40.4 / 38.5, 384 x 706 x 37 34.3 / 31.0; plain steps,
+//     which pay less for a run, runs of 2 of shape 1 (FP64 160^3 27.1 / 25.0);
+//   * between 512 and 896, and 1024 and 1152, where a last round would be nearly
+//     empty: shape 1, whose rounds are finer (FP64 192^3 46.8 / 42.2); just under
+//     1024 shape 0 again (FP32 908 x 168 x 175 69.0 / 66.2; plain, runs of 4 of
+//     shape 1);
+//   * more: shape 0 in runs of 8 (FP64 512^3 584 / 567, FP32 298 / 285), of 4
+//     where the step is plain (FP64 360 x 388 x 475 311 / 284);
+//   * rows just longer than a wave's, which leave over two fifths of their waves
+//     idle, run long in shape 0: FP64 136 x 748 x 425 plain 263.7 in runs of 4, 256.2
+//     in runs of 16.
+// Narrow rows, which fill at most three quarters of one wave (48 vectors), have
+// few points to a plane's halo loads: shape 1 keeps four waves per SIMD waiting
+// on them.  FP64 24 x 360 x 1157 130.7 / 114.7, plain 129.5 in runs of 4 / 102.9;
+// FP32 128 x 720 x 542 130.0 / 116.9.  With sums, rows of at most half a wave
+// run 16 planes where that leaves two rounds (FP64 24 x 720 x 2893 559 / 525).
+// FP32 rows of at most 48 points take single elements (31 x 360 x 896: 90.9 with
+// vectors, 84.4; plain 73.1 / 64.4; at 62 points 51.8 / 50.9).
+// The adjoint step that recomputes its state holds two stencil operands: four rows
+// per lane leave it one wave per SIMD, so the reverse sweep's steps take shape 1
+// up to the most workgroups with it (200 steps of 256^3 FP64 33.0 / 31.1 ms).
+// Past kSumBlocks or kPlainBlocks workgroups the runs grow, up to 64 planes.
 // DCP_TILE_SHAPE / DCP_TILE_ZC override the choice in tuning runs (with
 // DCP_TUNING=1).
-Tile pick_tile(int dtype, const Geo &g, bool vec_ok, int most, bool forward = false) {
-    const int wide = dtype == DCP_F64 ? 2 : 4;
-    int shape = env_int("DCP_TILE_SHAPE", -1);
-    const bool forced = shape >= 0 && shape < num_shapes();
-    if (!forced) shape = 1;
-    // (vectors on ragged rows: compiled for the two shapes chosen here)
-    const int vec = vec_ok && (g.nx % wide == 0 || shape <= 1) ? wide : 1;
+Tile pick_tile(int dtype, const Geo &g, bool vec_ok, StepUse use) {
+    const bool sums = use != kPlainStep;
+    const int wide = dtype == DCP_F64 ? 2 : 4, most = sums ? kSumBlocks : kPlainBlocks;
+    const int forced = env_int("DCP_TILE_SHAPE", -1);
+    int shape = forced >= 0 && forced < num_shapes() ? forced : -1;
+    // (vectors on ragged rows are compiled for the two shapes chosen here)
+    const bool one = !vec_ok || (dtype == DCP_F32 && g.nx <= 48) || (g.nx % wide != 0 && shape > 1);
+    const int vec = one ? 1 : wide;
+    auto blocks = [&](int sh, int z) {
+        const int nb = make_tile(g, vec, sh, z).nblk;
+        return nb < 0 ? INT32_MAX : nb;
+    };
+    auto at_least = [&](int sh, int z, int lo, int nb) {  // runs of z planes, halved down to lo while under nb workgroups
+        while (z > lo && blocks(sh, z) < nb) z /= 2;
+        return z;
+    };
     int zc = env_int("DCP_TILE_ZC", 0);
     if (zc <= 0) {
-        auto blocks = [&](int z) {
-            const int nb = make_tile(g, vec, shape, z).nblk;
-            return nb < 0 ? INT32_MAX : nb;
+        const int n8 = blocks(0, 8);
+        const int64_t span = (g.nx + 64 * vec - 1) / (64 * vec) * 64 * vec;  // points the row's waves could hold
+        auto pick = [&](int sh, int z) {
+            if (shape < 0) shape = sh;
+            zc = z;
         };
-        zc = 8;
-        while (zc > 2 && blocks(zc) < (dtype == DCP_F64 ? 1200 : 900)) zc /= 2;
-        if (zc == 2 && blocks(2) < 512) zc = 1;
-        if (!forced && blocks(zc) > most) shape = 0;
-        if (forward && !forced) {
-            const int narrow = shape;
-            shape = 0;
-            if (blocks(8) < 1500) shape = narrow;
-            else if (most > kSumBlocks) zc = 4;
-            else if (g.nz % 8 != 0) zc = dtype == DCP_F64 ? 7 : 6;
-            else zc = 8;
-            if (shape == 0 && zc < 8 && blocks(zc) > most) zc = 8;
+        auto few = [&] {
+            const int z = at_least(1, 8, 2, dtype == DCP_F64 ? 1200 : 900);
+            pick(1, z == 2 && blocks(1, 2) < 512 ? 1 : z);
+        };
+        if (one) pick(sums ? 0 : 1, sums ? at_least(0, 8, 1, 700) : at_least(1, 4, 1, 700));
+        else if (use == kRecomputeStep && blocks(1, 8) > most) pick(0, 8);
+        else if (use == kRecomputeStep || n8 < 410) few();
+        else if (n8 <= 512 && sums) pick(0, 8);
+        else if (n8 <= 512 && g.nx > 48 * vec) pick(1, 2);
+        else if (n8 <= 512) few();
+        else if (g.nx <= 48 * vec) {
+            const int z = sums && g.nx <= 32 * vec && blocks(1, 16) >= 2048 ? 16 : 8;
+            if (dtype == DCP_F64 && blocks(1, z) > most) pick(0, at_least(0, 64, 8, 2048));
+            else pick(1, z);
         }
-        while (zc < 64 && blocks(zc) > most) zc *= 2;
+        else if (n8 < 896) few();
+        else if (n8 < 1024) pick(sums ? 0 : 1, sums ? 8 : 4);
+        else if (n8 < 1152) pick(1, 8);
+        else if (10 * g.nx < 6 * span) pick(0, at_least(0, 64, 8, 2048));
+        else pick(0, sums ? 8 : 4);
+        while (zc < 64 && blocks(shape, zc) > most) zc *= 2;
+        if (forced != shape && blocks(shape, zc) > most) shape = 0;
     }
+    if (shape < 0) shape = 1;
     if (g.nz > 0 && zc > g.nz) zc = (int)g.nz;
     if (zc < 1) zc = 1;
     return make_tile(g, vec, shape, zc);
 }
 
-// Largest workgroup count over both vector widths and both kinds of step (workspace sizing must not
-// depend on pointer alignment).
-int max_blocks(int dtype, const Geo &g, int most) {
+// Largest workgroup count of a step with sums over both vector widths
+// (workspace sizing must not depend on pointer alignment).
+int max_blocks(int dtype, const Geo &g, StepUse use) {
     if (g.n == 0) return 0;
-    int nb = 0;
-    for (const bool vec : {true, false})
-        for (const bool forward : {true, false}) {
-            const Tile t = pick_tile(dtype, g, vec, most, forward);
-            if (t.nblk < 0) return -1;
-            if (t.nblk > nb) nb = t.nblk;
-        }
-    return nb;
+    const Tile a = pick_tile(dtype, g, true, use), b = pick_tile(dtype, g, false, use);
+    if (a.nblk < 0 || b.nblk < 0) return -1;
+    return a.nblk > b.nblk ? a.nblk : b.nblk;
 }
 
 // ---------------------------------------------------------- workspace layout
@@ -174,7 +208,7 @@ int layout_step(int dtype, int impl, const Geo &g, bool norms, StepWs *w) {
         off += 3 * align_up(g.bytes());
     }
     if (norms && g.n > 0) {
-        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumBlocks);
+        const int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumStep);
         if (nb < 0) return DCP_E_SHAPE;
         w->partials = off;
         off += align_up((size_t)nb * 2 * sizeof(double));
@@ -248,7 +282,7 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
         off += 3 * align_up(g.bytes());
     }
     if (norms) {
-        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumBlocks);
+        int nb = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : max_blocks(dtype, g, kSumStep);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (impl == DCP_FUSED && tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) &&
@@ -287,7 +321,7 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         return DCP_OK;
     }
     if (g.n > 0) {
-        int nb = max_blocks(dtype, g, kSumBlocks);
+        int nb = max_blocks(dtype, g, kSumStep);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) && tb.nblk > nb) nb = tb.nblk;
@@ -625,14 +659,13 @@ int step_common(int impl, int dtype, const void *u, const void *f, void *u_out, 
 
     double *partials = norms2 ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
     if (impl == DCP_FUSED) {
-        const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}),
-                                norms2 ? kSumBlocks : kPlainBlocks, true);
+        const Tile t = pick_tile(dtype, g, vec_ok_for(dtype, g, {u, f, u_out}), norms2 ? kSumStep : kPlainStep);
         DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, u, f, u_out, partials, st));
         if (norms2) DCP_TRY(launch_finalize(partials, t.nblk, t.nblk, 1, norms2, nullptr, 0, st));
     } else {
         void *tmp[3] = {at(ws, w.temps), at(ws, w.temps + align_up(fb)), at(ws, w.temps + 2 * align_up(fb))};
         const bool vok = vec_ok_for(dtype, g, {u, f, u_out, tmp[0], tmp[1], tmp[2]});
-        const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+        const Tile t = pick_tile(dtype, g, vok, kSumStep);
         const bool eok = ew_ok({u, f, u_out, tmp[0], tmp[1], tmp[2]});
         DCP_TRY(unfused_step(dtype, bc, g, *coeffs, t, eok, u, f, u_out, tmp, partials, st));
         if (norms2) {
@@ -664,7 +697,7 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         return DCP_OK;
     }
     const size_t fb = align_up(g.bytes());
-    int nb = max_blocks(dtype, g, kSumBlocks);
+    int nb = max_blocks(dtype, g, kRecomputeStep);
     if (nb < 0) return DCP_E_SHAPE;
     BlkTile bk;
     if (blk_for(dtype, g, 2, kLdsMax, &bk) && bk.nblk > nb) nb = bk.nblk;
@@ -894,7 +927,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     const bool vok = vec_ok_for(dtype, g, {u, f, buf, tmp[0], tmp[1], tmp[2], ckpt});
     bool eok = ew_ok({u, f, buf, tmp[0], tmp[1], tmp[2]});  // of every state and temporary
     for (int32_t c = 0; c < nslots; ++c) eok = eok && aligned16(slot(c));
-    const Tile t = pick_tile(dtype, g, vok, kSumBlocks, impl == DCP_FUSED);
+    const Tile t = pick_tile(dtype, g, vok, kSumStep);
     const int nblk_one = impl == DCP_UNFUSED ? ew_norm_blocks(g.n) : t.nblk;
     const int stride = w.nblk;  // partial slots per step (>= every kernel's workgroup count)
     double *partials = norms ? reinterpret_cast<double *>(at(ws, w.partials)) : nullptr;
@@ -1051,7 +1084,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     auto seg = [&](int32_t j) { return static_cast<void *>(at(ws, w.seg + (size_t)j * align_up(fb))); };
     auto slot = [&](int32_t c) { return static_cast<const void *>(static_cast<const char *>(ckpt) + (size_t)c * fb); };
     const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, lam[0], lam[1], lsum, ckpt, seg(0)});
-    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+    const Tile t = pick_tile(dtype, g, vok, kSumStep);
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
     double *sums = reinterpret_cast<double *>(at(ws, w.sums));
     const int stride = w.nblk;
@@ -1201,7 +1234,7 @@ int dcp_revolve_forward(int dtype, void *u, const void *f, int64_t nx, int64_t n
     const RevBufs B{ws, &w, nslots, align_up(fb)};
     void *scratch = at(ws, w.scratch);
     const bool vok = vec_ok_for(dtype, g, {u, f, ws});
-    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+    const Tile t = pick_tile(dtype, g, vok, kRecomputeStep);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, B.buf(kRvOrigin), 0.0, g.n, ew_ok({u, B.buf(kRvOrigin)}), st));
@@ -1266,7 +1299,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     void *lam[2] = {at(ws, w.lam), at(ws, w.lam + align_up(fb))};
     void *lsum = grad_f ? grad_f : (lsum_field ? static_cast<void *>(at(ws, w.lsum)) : nullptr);
     const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, grad_f, ws});
-    const Tile t = pick_tile(dtype, g, vok, kSumBlocks);
+    const Tile t = pick_tile(dtype, g, vok, kRecomputeStep);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
