@@ -2,6 +2,7 @@
 // checks, workspace layout, tile choice and the host drivers of the time
 // loop and of the checkpointed adjoint.  All device work is enqueued on the
 // caller's stream; nothing here synchronises or allocates device memory.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -217,10 +218,19 @@ int layout_step(int dtype, int impl, const Geo &g, bool norms, StepWs *w) {
     return DCP_OK;
 }
 
+// Steps whose workgroups' pairs of sums a workspace holds at once, at most T:
+// 16 MiB of them (512^3: 128 steps) and a pass's three at least.  Longer runs
+// reduce a batch when it is full, one launch in a batch's time, and the
+// workspace does not grow with the steps.
+int32_t sum_steps(int32_t T, int nblk) {
+    const size_t fit = ((size_t)16 << 20) / ((size_t)nblk * 2 * sizeof(double));
+    return (int32_t)std::min<size_t>((size_t)T, fit < 3 ? 3 : fit);
+}
+
 struct RunWs {
     size_t field = 0;     // ping-pong field
     size_t temps = 0;     // unfused temporaries
-    size_t partials = 0;  // [T][nblk][2]
+    size_t partials = 0;  // [sum_steps][nblk][2]
     int nblk = 0;
     size_t total = 0;
 };
@@ -296,7 +306,7 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
         }
         w->nblk = nb;
         w->partials = off;
-        off += align_up((size_t)T * nb * 2 * sizeof(double));
+        off += align_up((size_t)sum_steps(T, nb) * nb * 2 * sizeof(double));
     }
     w->total = off;
     return DCP_OK;
@@ -305,7 +315,7 @@ int layout_run(int dtype, int impl, const Geo &g, int32_t T, int32_t tblock, boo
 struct AdjWs {
     size_t lam = 0;       // 2 fields
     size_t seg = 0;       // k-1 fields
-    size_t partials = 0;  // [T][nblk][2]
+    size_t partials = 0;  // [sum_steps][nblk][2]
     size_t sums = 0;      // [T][2]
     size_t lsum = 0;      // 1 field: running sum of the adjoint inputs (when wanted there)
     size_t dot = 0;       // [ew_norm_blocks][2] + 2: partials of <sum, f>
@@ -334,7 +344,7 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         const int32_t kk = k < T ? k : T;
         off += (size_t)(kk - 1) * align_up(g.bytes());
         w->partials = off;
-        off += align_up((size_t)T * nb * 2 * sizeof(double));
+        off += align_up((size_t)sum_steps(T, nb) * nb * 2 * sizeof(double));
         if (lsum_field) {
             w->lsum = off;
             off += align_up(g.bytes());
@@ -364,6 +374,58 @@ int hip_status(hipError_t e) { return e == hipSuccess ? DCP_OK : DCP_E_HIP; }
         hipError_t e_ = (expr);                  \
         if (e_ != hipSuccess) return DCP_E_HIP;  \
     } while (0)
+
+// The per-workgroup pairs of sums of a sweep's steps, in the workspace's room for
+// sum_steps of them: step s in slot s mod that many, the steps held consecutive.
+// A batch is reduced when the next steps do not fit beside it, and at the end, in
+// a fixed order, one launch for each run of steps that share a workgroup count.
+class StepSums {
+  public:
+    StepSums(double *partials, int stride, int32_t T, int nblk, double *out0, double *out1, int mode, hipStream_t st)
+        : p_(partials), stride_(stride), cap_(stride > 0 ? sum_steps(T, stride) : 0), out0_(out0), out1_(out1),
+          mode_(mode), st_(st) {
+        if (p_) nblk_.assign((size_t)T, nblk);
+    }
+    // Takes steps lo .. hi - 1, next to those held.
+    hipError_t take(int32_t lo, int32_t hi) {
+        if (!p_) return hipSuccess;
+        if (std::max(hi, hi_) - std::min(lo, lo_) > cap_ || lo_ == hi_) {
+            if (hipError_t e = reduce()) return e;
+            lo_ = lo;
+            hi_ = hi;
+        } else {
+            lo_ = std::min(lo, lo_);
+            hi_ = std::max(hi, hi_);
+        }
+        return hipSuccess;
+    }
+    double *of(int32_t s) const { return p_ ? p_ + (size_t)(s % cap_) * stride_ * 2 : nullptr; }
+    void set(int32_t lo, int32_t hi, int nblk) {
+        if (p_) std::fill(nblk_.begin() + lo, nblk_.begin() + hi, nblk);
+    }
+    hipError_t reduce() {
+        for (int32_t s0 = lo_; s0 < hi_;) {
+            int32_t s1 = s0 + 1;
+            while (s1 < hi_ && s1 % cap_ != 0 && nblk_[s1] == nblk_[s0]) ++s1;
+            double *o0 = out0_ ? out0_ + (size_t)s0 * (mode_ == 2 ? 2 : 1) : nullptr;
+            if (hipError_t e = launch_finalize(of(s0), nblk_[s0], stride_, s1 - s0, o0, out1_ ? out1_ + s0 : nullptr,
+                                               mode_, st_))
+                return e;
+            s0 = s1;
+        }
+        lo_ = hi_ = 0;
+        return hipSuccess;
+    }
+
+  private:
+    double *p_;
+    int stride_;
+    int32_t cap_, lo_ = 0, hi_ = 0;
+    double *out0_, *out1_;
+    int mode_;
+    hipStream_t st_;
+    std::vector<int> nblk_;  // workgroups behind each step's pairs
+};
 
 StencilArgs fwd_args(const Geo &g, const dcp_coeffs &c, const Tile &t, const void *u, const void *f,
                      void *out, double *partials) {
@@ -717,7 +779,7 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         off += fb;
     }
     w->partials = off;
-    off += align_up((size_t)T * nb * 2 * sizeof(double));
+    off += align_up((size_t)sum_steps(T, nb) * nb * 2 * sizeof(double));
     w->sums = off;
     off += align_up((size_t)T * 2 * sizeof(double));
     w->dot = off;
@@ -940,9 +1002,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
     const TbTile &tb = pp.tb;
     const TbkTile &tk2 = pp.k2, &tk3 = pp.k3;
 
-    // workgroup count behind each step's partials, for the fixed-order finalize
-    std::vector<int> step_nblk;
-    if (norms) step_nblk.assign((size_t)T, nblk_one);
+    StepSums step_sums(partials, stride, T, nblk_one, energy, resid, 1, st);
 
     auto is_ckpt = [&](int32_t t) { return nslots > 0 && t % ckpt_every == 0 && t / ckpt_every < nslots; };
     if (nslots > 0) DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, slot(0), 0.0, g.n, ew_ok({u, slot(0)}), st));
@@ -951,7 +1011,8 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
         const int32_t len = pp.len_at(s, T);
         const int32_t se = s + len;
         void *nxt = is_ckpt(se) ? slot(se / ckpt_every) : ((cur == u) ? buf : u);
-        double *p = partials ? partials + (size_t)s * stride * 2 : nullptr;
+        DCP_TRY(step_sums.take(s, se));
+        double *p = step_sums.of(s);
         const bool blocks = (len == 3 && pp.use_b3) || (len == 2 && pp.use_b2);
         if (len == 3 || (len == 2 && (blocks || !use_tb))) {
             // checkpoints at the middle steps are stored by the pass itself
@@ -959,17 +1020,15 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
             const BlkTile &bk = len == 3 ? pp.b3 : pp.b2;
             void *mid[2] = {is_ckpt(s + 1) ? slot((s + 1) / ckpt_every) : nullptr,
                             len == 3 && is_ckpt(s + 2) ? slot((s + 2) / ckpt_every) : nullptr};
-            double *part[3] = {p, p ? p + (size_t)stride * 2 : nullptr, p ? p + (size_t)stride * 4 : nullptr};
+            double *part[3] = {p, step_sums.of(s + 1), len == 3 ? step_sums.of(s + 2) : nullptr};
             if (blocks) DCP_TRY(blk_fwd_pass(dtype, bc, g, *coeffs, bk, cur, f, nxt, mid, p ? part : nullptr, st));
             else DCP_TRY(tbk_fwd_pass(dtype, bc, g, *coeffs, tk, cur, f, nxt, mid, p ? part : nullptr, st));
-            if (norms)
-                for (int32_t i = s; i < se; ++i) step_nblk[i] = blocks ? bk.nblk : tk.nblk;
+            step_sums.set(s, se, blocks ? bk.nblk : tk.nblk);
         } else if (len == 2) {
             // a checkpoint at the middle step is stored by the pass itself
             void *mid = is_ckpt(s + 1) ? slot((s + 1) / ckpt_every) : nullptr;
-            DCP_TRY(tb_fwd_pass(dtype, bc, g, *coeffs, tb, cur, f, nxt, mid, p,
-                                p ? p + (size_t)stride * 2 : nullptr, st));
-            if (norms) step_nblk[s] = step_nblk[s + 1] = tb.nblk;
+            DCP_TRY(tb_fwd_pass(dtype, bc, g, *coeffs, tb, cur, f, nxt, mid, p, step_sums.of(s + 1), st));
+            step_sums.set(s, se, tb.nblk);
         } else if (impl == DCP_FUSED) {
             DCP_TRY(fused_step(dtype, bc, g, *coeffs, t, cur, f, nxt, p, st));
         } else {
@@ -979,16 +1038,7 @@ int dcp_run(int dtype, int impl, void *u, const void *f, int64_t nx, int64_t ny,
         s = se;
     }
     if (cur != u) DCP_TRY(launch_ew(dtype, EW_COPY, cur, nullptr, u, 0.0, g.n, ew_ok({cur, u}), st));
-    if (norms) {
-        // one fixed-order reduction per run of steps that share a workgroup count
-        for (int32_t s0 = 0; s0 < T;) {
-            int32_t s1 = s0 + 1;
-            while (s1 < T && step_nblk[s1] == step_nblk[s0]) ++s1;
-            DCP_TRY(launch_finalize(partials + (size_t)s0 * stride * 2, step_nblk[s0], stride, s1 - s0,
-                                    energy ? energy + s0 : nullptr, resid ? resid + s0 : nullptr, 1, st));
-            s0 = s1;
-        }
-    }
+    DCP_TRY(step_sums.reduce());
     return DCP_OK;
 }
 
@@ -1116,7 +1166,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     // segment waits for that segment (its upper state is a checkpoint slot).
     // Every step's parameter sums therefore come from the same kernel with the
     // same tiling for any k, and the gradient does not depend on k bit for bit.
-    std::vector<int> step_nblk((size_t)T, t.nblk);
+    StepSums step_sums(partials, stride, T, t.nblk, sums, nullptr, 2, st);
     const int adj_op = lsum ? SOP_ADJL : SOP_ADJ;
     aa.lam = lsum;
     ta.lam = lsum;
@@ -1146,6 +1196,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
             const bool pair = ap.nblk && (s & 1) && s >= 1;
             if (pair && s - 1 < t0) break;  // the lower step lives in the previous segment
             const int32_t se = pair ? s - 1 : s;
+            DCP_TRY(step_sums.take(se, s + 1));
             void *out = (se == 0) ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
             if (pair) {
                 ta.u = lcur;
@@ -1153,16 +1204,16 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
                 ta.g2 = state(s - 1);
                 ta.out = out;
                 ta.mid = nullptr;
-                ta.part1 = partials + (size_t)s * stride * 2;
-                ta.part2 = partials + (size_t)(s - 1) * stride * 2;
+                ta.part1 = step_sums.of(s);
+                ta.part2 = step_sums.of(s - 1);
                 ta.lam_first = lam_first;
                 DCP_TRY(adj_pair(dtype, adj_op, bc, ap, ta, st));
-                step_nblk[s] = step_nblk[s - 1] = ap.nblk;
+                step_sums.set(s - 1, s + 1, ap.nblk);
             } else {
                 aa.s = lcur;
                 aa.q = state(s);
                 aa.out = out;
-                aa.partials = partials + (size_t)s * stride * 2;
+                aa.partials = step_sums.of(s);
                 aa.lam_first = lam_first;
                 DCP_TRY(launch_stencil(dtype, adj_op, bc, true, t, aa, st));
             }
@@ -1172,13 +1223,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
         }
     }
     // per-step sums in a fixed order, then over the steps in a fixed order
-    for (int32_t s0 = 0; s0 < T;) {
-        int32_t s1 = s0 + 1;
-        while (s1 < T && step_nblk[s1] == step_nblk[s0]) ++s1;
-        DCP_TRY(launch_finalize(partials + (size_t)s0 * stride * 2, step_nblk[s0], stride, s1 - s0,
-                                sums + 2 * (size_t)s0, nullptr, 2, st));
-        s0 = s1;
-    }
+    DCP_TRY(step_sums.reduce());
     DCP_TRY(launch_grad_finalize(sums, T, c.dt / (c.h * c.h), -c.dt, grad_ab, st));
     if (lsum) {
         // dL/dgamma = dt * <sum, f> (fixed-order double reduction), then
@@ -1329,7 +1374,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     ta.nslab = ap.tb.nslab;
     ta.zc = ap.tb.zc;
     ta.lam = lsum;
-    std::vector<int> step_nblk((size_t)T, t.nblk);
+    StepSums step_sums(partials, stride, T, t.nblk, sums, nullptr, 2, st);
     const int adj_op = lsum ? SOP_ADJL : SOP_ADJ;
     const int adj_rop = lsum ? SOP_ADJLR : SOP_ADJR;
     int lam_first = 1;
@@ -1387,10 +1432,11 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
         // adjoint step s with u_s in buffer src, or recomputed from u_{s-1};
         // or steps s and s - 1 when the next operation is step s - 1
         const RvOp &adj = folded ? ops[i + 1] : op;
-        const int64_t s = adj.t0;
+        const int32_t s = (int32_t)adj.t0;
         const bool pair = !folded && ap.nblk && i + 1 < ops.size() && ops[i + 1].kind == kRvAdjoint &&
                           ops[i + 1].t0 == s - 1;
-        const int64_t se = pair ? s - 1 : s;
+        const int32_t se = pair ? s - 1 : s;
+        DCP_TRY(step_sums.take(se, s + 1));
         void *out = (se == 0) ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
         if (pair) {
             ta.u = lcur;
@@ -1398,17 +1444,17 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
             ta.g2 = B.buf(ops[i + 1].src);
             ta.out = out;
             ta.mid = nullptr;
-            ta.part1 = partials + (size_t)s * stride * 2;
-            ta.part2 = partials + (size_t)(s - 1) * stride * 2;
+            ta.part1 = step_sums.of(s);
+            ta.part2 = step_sums.of(s - 1);
             ta.lam_first = lam_first;
             DCP_TRY(adj_pair(dtype, adj_op, bc, ap, ta, st));
-            step_nblk[s] = step_nblk[s - 1] = ap.nblk;
+            step_sums.set(s - 1, s + 1, ap.nblk);
         } else {
             aa.s = lcur;
             aa.q = folded ? f : B.buf(adj.src);
             aa.s2 = folded ? B.buf(op.src) : nullptr;
             aa.out = out;
-            aa.partials = partials + (size_t)s * stride * 2;
+            aa.partials = step_sums.of(s);
             aa.lam_first = lam_first;
             DCP_TRY(launch_stencil(dtype, folded ? adj_rop : adj_op, bc, true, t, aa, st));
         }
@@ -1417,13 +1463,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
         if (folded || pair) ++i;
     }
     // per-step sums in a fixed order, then over the steps in a fixed order
-    for (int32_t s0 = 0; s0 < T;) {
-        int32_t s1 = s0 + 1;
-        while (s1 < T && step_nblk[s1] == step_nblk[s0]) ++s1;
-        DCP_TRY(launch_finalize(partials + (size_t)s0 * stride * 2, step_nblk[s0], stride, s1 - s0,
-                                sums + 2 * (size_t)s0, nullptr, 2, st));
-        s0 = s1;
-    }
+    DCP_TRY(step_sums.reduce());
     DCP_TRY(launch_grad_finalize(sums, T, c.dt / (c.h * c.h), -c.dt, grad_ab, st));
     if (lsum) {
         if (grad_gamma) {
