@@ -110,16 +110,22 @@ __global__ void __launch_bounds__(kLanes) block_kernel(BlkArgs a) {
     // level; lanes that own nothing drop their sums at the end.
 #pragma unroll
     for (int s = 1; s <= B; ++s) {
+        // The planes' LDS addresses are kept from one step to the next, in 34
+        // registers; the form that has none left for them computes them anew (it
+        // spilled nine, which made the loads wait for each other; elsewhere that
+        // costs up to 3% of a run).
+        int fp = FP;
+        if constexpr (B == 3 && BZ == 8 && sizeof(T) == 8 && BC == 0 && RED) asm volatile("" : "+s"(fp));
         if (s > 1) __syncthreads();
         if (in) {
 #pragma unroll
-            for (int z = s; z < FZ - s; ++z) SM[(z - 1) * FP + tid] = cur[z];
+            for (int z = s; z < FZ - s; ++z) SM[(z - 1) * fp + tid] = cur[z];
         }
         __syncthreads();
         T below = cur[s - 1];
 #pragma unroll
         for (int z = s; z < FZ - s; ++z) {
-            const T *P = SM + (z - 1) * FP;
+            const T *P = SM + (z - 1) * fp;
             const T c = cur[z];
             const T s6 = ((P[xm] + P[xp]) + (P[ym] + P[yp])) + (below + cur[z + 1]);
             const T lapn = fma(T(-6), c, s6);
@@ -155,7 +161,7 @@ __global__ void __launch_bounds__(kLanes) block_kernel(BlkArgs a) {
             if constexpr (BC == 0) nv = ghost || gz < 0 || gz >= nz ? T(0) : nv;
             below = c;
             cur[z] = nv;
-            // four planes' LDS reads in flight; more only spill
+            // four planes' LDS reads in flight
             if ((z - s) % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
         void *dst = s < B ? a.mid[s < B ? s - 1 : 0] : a.out;

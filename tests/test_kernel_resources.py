@@ -70,3 +70,9 @@ def test_one_step_kernel_with_sums_holds_four_waves(kernels, lanes, bc, op):
     # whole rows, two rows per lane
     for name, k in _find(kernels, rf"stencil_kernelI{lanes}Li1ELi4ELi2ELi{bc}ELi{op}ELb1E(Lb0E)?EE").items():
         assert _waves(k) >= 4 and k[".vgpr_spill_count"] == 0, (name, k[".vgpr_count"])
+
+
+def test_block_passes_spill_nothing(kernels):
+    # (the loads of a block go out together only while every value has a register)
+    for name, k in _find(kernels, r"12block_kernelI").items():
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, name
