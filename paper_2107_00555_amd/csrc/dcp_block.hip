@@ -89,7 +89,13 @@ __global__ void __launch_bounds__(kLanes) block_kernel(BlkArgs a) {
     }
     if constexpr (LAM) {
 #pragma unroll
-        for (int z = 0; z < BZ; ++z) lv[z] = a.lam_first ? T(0) : plane(a.lam, z + B)[col];
+        for (int z = 0; z < BZ; ++z) lv[z] = T(0);
+        // the running sum is read where it is written: another block's points are
+        // being changed meanwhile
+        if (own && !a.lam_first) {
+#pragma unroll
+            for (int z = 0; z < BZ; ++z) lv[z] = plane(a.lam, z + B)[col];
+        }
     }
     if constexpr (BC == 0) {
 #pragma unroll
