@@ -156,6 +156,13 @@ __device__ __forceinline__ T k_fwd(T c, T xm, T xp, T ym, T yp, T zm, T zp, T fq
 constexpr unsigned kValid = 1u, kOwned = 16u, kGhost = 32u, kTwice = 64u;
 constexpr int kColShift = 8;
 
+// The ring form's planes: their bytes at most, and the offset that a dropped
+// 16-byte store is given, past every plane's bound in each of its four dwords
+// without wrapping.
+constexpr uint32_t kPlaneLimit = 0x7fffffffu, kDropOffset = 0x80000000u;
+static_assert(kDropOffset >= kPlaneLimit && kDropOffset % 4 == 0 && kDropOffset <= UINT32_MAX - 15,
+              "a dropped store lies past its buffer in every dword");
+
 template <typename T, int VEC, int B, int NT, int KM, int BC, bool SEG, bool RAG, bool RED>
 __global__ void __launch_bounds__(NT) tbk_kernel(TbkArgs a) {
     static_assert(B >= 2 && B <= 3, "two or three steps per pass");
@@ -530,7 +537,7 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     }
 
     // Every lane loads, from a uniform plane base plus its chunk's 32-bit
-    // byte offset in the plane (the planner keeps a plane under 4 GiB for
+    // byte offset in the plane (the planner keeps a plane under kPlaneLimit for
     // this kernel), so the ring registers have one writer and the loads'
     // waits can be counted instead of drained.  Chunks outside the grid
     // (ghost rows, columns or planes) and lanes past the frame read a valid
@@ -552,7 +559,7 @@ __global__ void __launch_bounds__(NT) tbr_kernel(TbkArgs a) {
     const unsigned plane_bytes = (unsigned)(sz * (int64_t)sizeof(T));
     unsigned sb[KM];
 #pragma unroll
-    for (int k = 0; k < KM; ++k) sb[k] = flags[k] & kOwned ? gb[k] : ~0u;
+    for (int k = 0; k < KM; ++k) sb[k] = flags[k] & kOwned ? gb[k] : kDropOffset;
     auto sink_of = [&](void *field, int p, bool on) {
         T *base = static_cast<T *>(field) + (int64_t)(on ? p : 0) * sz;
         return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, on && field ? plane_bytes : 0u, 0x00027000);
@@ -874,8 +881,8 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
     // ragged rows: the three-step ring form and the two-step plain form only
     if (shift && !(B == 3 ? ln.ring : ln.nt == 1024)) return false;
     // the ring form addresses a chunk as a plane base plus a 32-bit offset
-    // (the tile limits below already keep its planes under 1 GiB)
-    if (ln.ring && nx * ny * esz > (int64_t)UINT32_MAX) return false;
+    // (the tile limits below already keep its planes under it)
+    if (ln.ring && nx * ny * esz > (int64_t)kPlaneLimit) return false;
     double best = 1e300;
     bool found = false;
     const bool sectors = ch % 4 == 0 && !shift;  // every row starts a 64-byte sector
