@@ -35,6 +35,8 @@
 // The norms of all B steps are reduced over the owned points only.
 #include "dcp_internal.h"
 
+#include <algorithm>
+
 namespace dcp {
 namespace {
 
@@ -886,9 +888,8 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
     double best = 1e300;
     bool found = false;
     const bool sectors = ch % 4 == 0 && !shift;  // every row starts a 64-byte sector
-    auto consider = [&](int64_t wc, int ty) {
+    auto consider = [&](int64_t wc, int64_t nseg, int ty) {
         const bool seg = wc < ch;
-        const int64_t nseg = (ch + wc - 1) / wc;
         // a chunk of a ragged row lies inside it whole: at least two segments,
         // the last one wider than the halo
         if (shift && (!seg || ch - (nseg - 1) * wc < halo + 1 || wc < halo + 1)) return;
@@ -954,7 +955,7 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
         for (int64_t wc : widths) {
             if (wc > ch || (force_wc > 0 && (wc < ch ? wc != force_wc : force_wc < ch))) continue;
             for (int ty : {16, 8, 4})
-                if (force_ty <= 0 || ty == force_ty) consider(wc, ty);
+                if (force_ty <= 0 || ty == force_ty) consider(wc, (ch + wc - 1) / wc, ty);
         }
         return found;
     }
@@ -964,12 +965,21 @@ bool tbk_plan(int dtype, int B, int64_t nx, int64_t ny, int64_t nz, bool vec_ok,
     // fewest points, three steps per pass, us per step: FP64 160^3 16.1 -> 11.7,
     // 192^3 20.7 -> 16.6, 256^3 34.3 -> 30.4, 320^3 66.8 -> 55.2, 1030 x 515 x
     // 200 298 -> 175, 512^3 the same tiles; FP32 320^3 46.7 -> 33.3.
-    for (int64_t nseg = 1; nseg <= ch; ++nseg) {
-        const int64_t wc = (ch + nseg - 1) / nseg;
-        if (nseg > 1 && wc < (shift ? 4 : 8)) break;
-        // (only the heights whose frame the lanes hold)
-        const int64_t fit = (int64_t)ln.nt * ln.km / (nseg > 1 ? wc + 2 * halo : ch) - 2 * B;
-        for (int ty = (int)(fit < 24 ? fit : 24); ty >= 2; --ty) consider(wc, ty);
+    // Each width once, from the widest whose frame of two rows the lanes hold: a
+    // plan of a row of any length takes as long (16384 x 64 x 64 1.8 ms with every
+    // number of segments tried, 2^24 x 1 x 1 1.4 s).
+    auto heights = [&](int64_t wc, int64_t nseg, int64_t chf) {  // (only those whose frame the lanes hold)
+        const int64_t fit = (int64_t)ln.nt * ln.km / chf - 2 * B;
+        for (int ty = (int)(fit < 24 ? fit : 24); ty >= 2; --ty) consider(wc, nseg, ty);
+    };
+    heights(ch, 1, ch);
+    const int64_t widest = (int64_t)ln.nt * ln.km / (2 + 2 * B) - 2 * halo;
+    const int64_t narrowest = shift ? 4 : 8;
+    for (int64_t w = std::min(widest, ch - 1); w >= narrowest;) {
+        const int64_t nseg = (ch + w - 1) / w, wc = (ch + nseg - 1) / nseg;  // the same number of segments, even
+        if (wc < narrowest) break;
+        heights(wc, nseg, wc + 2 * halo);
+        w = wc - 1;
     }
     return found;
 }
