@@ -277,9 +277,25 @@ __global__ void __launch_bounds__(1024, RPL <= 4 ? 8 : 4) j2_kernel(J2Args a) {
         double va[RPL][VEC], vb[RPL][VEC];
         load(a.ain, va);
         // B: its own values when the pass starts with A, else only the boundary
-        // cells count (its interior is written before it is read)
-        if (a.phase || decltype(masked)::value) {
-            load(a.phase ? a.bin : a.bfix, vb);
+        // cells count (its interior is written before it is read).  A tile that
+        // holds some reads its rows' end cells in every lane, without a guard: on a
+        // narrow array most tiles do, and reading their whole rows cost them
+        // another array's traffic (20000 x 600, 2 half-steps per pass: 1136 us, 1019
+        // with a guard for each cell).
+        if (a.phase) {
+            load(a.bin, vb);
+        } else if constexpr (decltype(masked)::value) {
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const int64_t i = gr + r;
+                const bool whole = i <= 0 || i >= n0 - 1;  // a boundary row
+                const double *rb = a.bfix + min(max(i, (int64_t)0), n0 - 1) * n1;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const int j = gc + v, end = j <= 0 ? 0 : n1 - 1;
+                    vb[r][v] = rb[whole ? min(max(j, 0), n1 - 1) : end];
+                }
+            }
         } else {
 #pragma unroll
             for (int r = 0; r < RPL; ++r) vb[r][0] = vb[r][1] = 0.0;
@@ -604,16 +620,18 @@ int j1_pick_k(int64_t n, int64_t hh) {
 }
 
 // Rows per lane of the 2D region tiles (16 waves, so 32 to 128 rows of 128
-// columns): the choice with the least work for the busiest CU, in rows of a
-// tile, halo rows included.  A pass costs about 28 rows' worth per tile for
-// the launch, loads and stores.  Tiles of up to four rows per lane (64 VGPRs)
-// run two to a CU and hide that behind each other's updates, the more so over
-// several rounds.  Measured with 12 half-steps, us per pass: 300^2 8.1 with
-// two rows per lane, 12.0 with four, 20.9 with eight; 1300^2 18.3 with six
-// (247 tiles), 19.5 with four (429), 19.7 with three; 2000^2 33 with four,
-// 39 with seven; 5001 x 4999 181 with four, 218 with seven.  DCP_J2_CFG = 0,
-// 1 or 2 forces 4, 6 or 8 rows per lane where the halo leaves a tile (tuning
-// runs only).
+// columns): the least time by a price for a tile and for the tiles of one CU,
+// fitted to 111 arrays of 100 to 20,000 rows and columns with 1, 4, 8 and 12
+// half-steps per pass (most of them narrow), where its choice takes 1.000 to 1.005
+// times the fastest in the mean, at most 1.07.  A tile takes 1 + rows per lane *
+// (1.25 + 0.04 * half-steps), whether it holds boundary cells or not.  Tiles of up
+// to four rows per lane (64 VGPRs) run two to a CU and hide each other's waits: each
+// beyond the CU's first adds half a tile's time (48 to 52%).  Taller ones run one by
+// one.  us per pass, in runs of 8 (118 x 9505) and 12 half-steps: 118 x 9505 11.9 with
+// four rows per lane, 14.7 with two; 200 x 3000 12.7 with four, 17.1 with six; 300^2
+// 8.1 with two, 12.0 with four; 1300^2 18.3 with six (247 tiles), 19.5 with four
+// (429); 2000^2 33 with four, 39 with seven.  DCP_J2_CFG = 0, 1 or 2 forces 4, 6 or 8
+// rows per lane where the halo leaves a tile (tuning runs only).
 int j2_pick_rpl(int64_t n0, int64_t n1, int64_t hh) {
     const char *fc = dcp::tuning_env("DCP_J2_CFG");
     if (fc && *fc) {
@@ -626,9 +644,9 @@ int j2_pick_rpl(int64_t n0, int64_t n1, int64_t hh) {
         const int64_t rows = 16 * rpl, inner_r = rows - 2 * hh, inner_c = kJ2C - 2 * hh;
         if (inner_r <= 0) continue;
         const double tiles = (double)((n0 + inner_r - 1) / inner_r) * (double)((n1 + inner_c - 1) / inner_c);
-        const double per_cu = std::ceil(tiles / 256.0);
-        const double x = rpl > 4 ? per_cu * (double)(rows + 28)
-                                 : per_cu <= 2.0 ? per_cu * (double)rows + 28.0 : 0.87 * per_cu * (double)rows;
+        const double per_cu = std::ceil(tiles / 256.0), tile = 1.0 + rpl * (1.25 + 0.04 * (double)hh);
+        const double x = rpl <= 4 ? tile * (1.0 + (0.44 + 0.02 * rpl) * (per_cu - 1.0))
+                                  : tile * 0.5 * (per_cu + std::max(1.0, tiles / 256.0));
         if (x < cost) {
             cost = x;
             best = rpl;
