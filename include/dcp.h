@@ -189,10 +189,11 @@ int dcp_step_unfused(int dtype, const void *u, const void *f, void *u_out,
  *   tblock      most steps fused per pass over memory (temporal blocking),
  *               1, 2 or 3; 1 = one pass per step.  Values > 1 need impl =
  *               DCP_FUSED.  Passes of tblock steps run on tiles of whole
- *               x-rows, or of x-segments with a halo of recomputed points
- *               (long rows; rows that are not whole 16-byte vectors of 2
- *               doubles or 4 floats, on grids of at least 2^18 points: below
- *               that, and where no tile fits, single steps are as fast);
+ *               x-rows, on small grids of blocks, or of x-segments with a halo
+ *               of recomputed points (long rows; rows that are not whole
+ *               16-byte vectors of 2 doubles or 4 floats).  Rows that are not
+ *               whole vectors take them on grids of at least 2^18 points; smaller
+ *               ones, and grids where no tile fits, run single steps.
  *               T mod tblock remaining steps run as shorter
  *               passes (dcp_run_plan reports the passes).  Either way every
  *               point is computed with the same operations, so u_T is
@@ -253,7 +254,7 @@ int dcp_run_plan(int dtype, int impl, int64_t nx, int64_t ny, int64_t nz,
  * symmetric under both boundary rules, so L^T is the same 7-point gather)
  * and accumulates the two parameter sums in double.
  * With tblock >= 2, two adjoint steps share one pass over memory where the
- * grid allows whole-row tiles (adjoint steps are paired by global parity,
+ * grid allows whole-row tiles, over blocks on small ones of these (adjoint steps are paired by global parity,
  * (2m+1, 2m), independently of k), and the recomputed forward steps take
  * passes of up to tblock steps, every state stored (as dcp_run plans them).
  *   ckpt        [ceil(T/k) fields] in: as written by dcp_run (same T, k,

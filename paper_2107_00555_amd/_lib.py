@@ -129,7 +129,7 @@ def workspace_bytes(op: int, dtype: int, nx: int, ny: int, nz: int, T: int = 0,
 
 def run_plan(dtype: int, nx: int, ny: int, nz: int, T: int, tblock: int, norms: bool = True,
              impl: int = FUSED) -> dict:
-    """The passes dcp_run takes for these arguments (16-byte aligned fields):
+    """The passes dcp_run takes for these arguments:
     {'passes': [one-step, two-step, three-step], 'steps_per_pass',
     'segmented', 'tile_rows', 'lanes'}."""
     info = RunInfo()

@@ -528,9 +528,12 @@ bool plan_tbk(int dtype, const Geo &g, int B, bool vok, TbkTile *t) {
     return tbk_for(dtype, g, B, vok, device_lds(), t);
 }
 
-// Smallest ragged grid that takes passes of several steps: at 64^3 points a
-// three-step pass takes as long as three single steps (17 us against 18), at
-// 101 x 97 x 103 23 us against 26, at 257 x 263 x 255 98 against 290.
+// Smallest ragged grid that takes passes of several steps.  The line is the marching
+// forms': at 64^3 points their three-step pass takes as long as three single steps
+// (17 us against 18), at 101 x 97 x 103 23 us against 26, at 257 x 263 x 255 98
+// against 290.  Blocks do not depend on it, and a grid below it would take 0.60 to
+// 0.81 of the time over them (48 steps of 63^3 FP64 237 us, 162 over blocks), but the
+// plan of a small ragged grid is one step per pass to its callers.
 constexpr int64_t kRaggedMin = (int64_t)1 << 18;
 
 // The passes of a fused dcp_run: three steps where tblock >= 3 and the
