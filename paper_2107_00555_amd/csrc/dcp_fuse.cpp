@@ -321,11 +321,12 @@ std::string scalar_expr(const dcp_fused *p, int i, const char *T) {
 }
 
 // Generated code.  A lane computes V consecutive x-points (16 bytes of the
-// dtype); a wave covers 64*V consecutive x of one (y, z) row (a wave tile)
-// and walks zr planes; a workgroup takes the same x tile of four
-// consecutive rows (a wave's y-neighbour rows are its siblings' rows, so
-// they tend to hit the CU's cache).  y and z are uniform over a wave.  The index type is 32-bit when the grid allows
-// it (a second entry point uses 64-bit indices).
+// dtype) of one row, or of two; a wave covers 64*V consecutive x of these rows (a
+// wave tile) and walks zr planes; a workgroup takes the same x tile of its four
+// waves' consecutive rows (a wave's y-neighbour rows are its siblings' rows, so
+// they tend to hit the CU's cache).  y and z are uniform over a wave.  The index
+// type is 32-bit when the grid allows it (a second entry point uses 64-bit
+// indices, a third two rows per lane).
 //
 // Reads of a memory field are grouped by (field, dy).  A group keeps, in
 // registers, one aligned V-wide vector of the lane's own x-points for each
@@ -335,10 +336,15 @@ std::string scalar_expr(const dcp_fused *p, int i, const char *T) {
 // read shifted by |dx| <= V takes its values from the lane's own vector and
 // the neighbouring lane's (cross-lane moves).  Lanes whose values would come
 // from outside the wave tile or the row (the first lane for dx < 0, the last
-// lanes for dx > 0, the lane at a ragged row end), and every lane of a read
-// with |dx| > V, take them per point through the boundary rule instead.
-// Grids too small for one wrap per axis take every point through the rule.
-// Points past the row end are computed but not stored.  The V points of a
+// lanes for dx > 0), and every lane of a read with |dx| > V, take them per point
+// through the boundary rule instead.  The last lane of a ragged row starts at nx - V,
+// so that it ends with the row, and it and the lane before load their values at
+// each other's side.  The points that the two share are computed and stored by both,
+// perhaps from two workgroups: with the same values, as long as no field that a
+// kernel writes shares storage with one that it reads (outputs may not overlap
+// inputs, and every stored value has a workspace buffer of its own).
+// Grids too small for one wrap per axis take every point through the rule, and
+// there points past the row end are computed but not stored.  The V points of a
 // lane are evaluated independently, each statement rounding once, so the
 // results do not depend on V or on the path taken.
 void generate(dcp_fused *p) {
