@@ -1,11 +1,14 @@
 """jacobi_2d's region tiles: the height chosen against the heights it can be
 forced to, on narrow arrays above all, and what a pass over a narrow array
-costs, whose tiles nearly all hold boundary cells.
+costs, whose tiles nearly all hold boundary cells; rows of odd length.
 """
+import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, say
+import oracle
+from gpu_util import DEV, say, to_dev, to_host
+from paper_2107_00555_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +60,19 @@ def test_narrow_array_moves_no_more(monkeypatch):
     print(f"square {square:.0f}, narrow {narrow:.0f}")
     # the column halo: 600 columns are five tiles of 124, 20 of them idle (3%)
     assert narrow <= 1.15 * square
+
+
+@pytest.mark.parametrize("shape", [(257, 511), (333, 261), (40, 1001), (1001, 33), (130, 129)])
+@pytest.mark.parametrize("tblock", [1, 2, 5, 8, 16])
+def test_region_tiles_on_odd_rows(monkeypatch, shape, tblock):
+    # the row march takes odd rows too: the tiles are forced
+    from paper_2107_00555_amd import api
+    monkeypatch.setenv("DCP_TUNING", "1")
+    monkeypatch.setenv("DCP_J2_MODE", "1")
+    A, B = inputs.jacobi_fields(2, shape[0], seed=3, n1=shape[1])
+    for tsteps in (2, 14):
+        say("jacobi_2d odd rows", shape, tblock, tsteps)
+        a, b = to_dev(A), to_dev(B)
+        api.jacobi_2d(a, b, tsteps, tblock)
+        want = oracle.jacobi_2d(tsteps, A, B)
+        assert np.array_equal(to_host(a), want[0]) and np.array_equal(to_host(b), want[1])
