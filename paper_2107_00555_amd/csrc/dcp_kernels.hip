@@ -132,7 +132,8 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 // and adjoint forms with sums from 126 and 128 registers to 130, four waves
 // per SIMD to three.
 template <typename T, int VEC, int BXW, int BY, int RY, int BC, int OP, bool RED, bool RAG>
-__global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
+__global__ void __launch_bounds__(64 * BXW * BY, RAG && VEC == 4 && RY == 2 && OP == SOP_ADJL ? 4 : 1)
+    stencil_kernel(StencilArgs a) {
     static_assert(!RAG || VEC > 1, "single elements have no ragged rows");
     constexpr int NW = BXW * BY;
     const int tid = threadIdx.x;
@@ -333,8 +334,11 @@ __global__ void __launch_bounds__(64 * BXW * BY) stencil_kernel(StencilArgs a) {
                         }
                     }
                     store_vec_nt<T, VEC>(O + z * sz + (yf + r) * sy + x0, res);
-                    if constexpr (LSUM) {
+                    if (LSUM && a.lam) {
                         // running sum of the adjoint inputs: lam += lambda_{t+1}
+                        // (never null here: the test keeps the sum's loads in a block
+                        // of their own, without which they took the FP32 form from 126
+                        // registers to 132, and from four waves per SIMD to three)
                         T *lp = static_cast<T *>(a.lam) + z * sz + (yf + r) * sy + x0;
                         if (RAG && sh) {  // the lane before adds to the first points
 #pragma unroll

@@ -72,6 +72,13 @@ def test_one_step_kernel_with_sums_holds_four_waves(kernels, lanes, bc, op):
         assert _waves(k) >= 4 and k[".vgpr_spill_count"] == 0, (name, k[".vgpr_count"])
 
 
+@pytest.mark.parametrize("bc", [0, 1])
+def test_adjoint_step_with_running_sum_holds_four_waves(kernels, bc):
+    # FP32, whole rows and ragged ones
+    for name, k in _find(kernels, rf"stencil_kernelIfLi4ELi1ELi4ELi2ELi{bc}ELi3ELb1E").items():
+        assert _waves(k) >= 4 and k[".vgpr_spill_count"] == 0, (name, k[".vgpr_count"])
+
+
 def test_block_passes_spill_nothing(kernels):
     # (the loads of a block go out together only while every value has a register)
     for name, k in _find(kernels, r"12block_kernelI").items():
