@@ -94,9 +94,9 @@ Tile make_tile(const Geo &g, int vec, int shape, int zc) {
 // stored), and of one without.
 constexpr int kSumBlocks = 8192, kPlainBlocks = 32768;
 
-// What a tile's step does: no sums, sums, or the reverse sweep's adjoint step
-// that may recompute its state.
-enum StepUse { kPlainStep, kSumStep, kRecomputeStep };
+// What a tile's step does: a forward step without sums or with them, or an adjoint
+// step.
+enum StepUse { kPlainStep, kSumStep, kAdjointStep };
 
 // Tile of the one-step kernels.  A wave covers 64 vectors of one row; a lane
 // holds two rows (shape 1: 8 rows per workgroup, four waves per SIMD) or four
@@ -127,9 +127,15 @@ enum StepUse { kPlainStep, kSumStep, kRecomputeStep };
 // run 16 planes where that leaves two rounds (FP64 24 x 720 x 2893 559 / 525).
 // FP32 rows of at most 48 points take single elements (31 x 360 x 896: 90.9 with
 // vectors, 84.4; plain 73.1 / 64.4; at 62 points 51.8 / 50.9).
-// The adjoint step that recomputes its state holds two stencil operands: four rows
-// per lane leave it one wave per SIMD, so the reverse sweep's steps take shape 1
-// up to the most workgroups with it (200 steps of 256^3 FP64 33.0 / 31.1 ms).
+// Adjoint steps hold more registers, the more with the running sum of their inputs or
+// where they recompute their state (which leaves four rows per lane one wave per
+// SIMD): they take shape 1 as grids under 410 do, and shape 0 where that would be too
+// many workgroups.  FP64 992 x 72 x 235 160 / 142, FP32 231 x 515 x 273 with the sum 237 /
+// 181, 200 steps of the reverse sweep of 256^3 FP64 33.0 / 31.1 ms; only one full round is
+// the better in shape 0 without the sum (FP32 256^3 40.0 / 41.6).  All of them take one
+// tile: the parameter sums are the same, bit for bit, with the running sum and without.
+// Single elements on FP32 rows of at most 64 points that are not whole vectors (45 x
+// 400 x 666 80 / 74, with the sum 149 / 144; 63 x 400 x 476 60 / 55 and 135 / 111).
 // Past kSumBlocks or kPlainBlocks workgroups the runs grow, up to 64 planes.
 // DCP_TILE_SHAPE / DCP_TILE_ZC override the choice in tuning runs (with
 // DCP_TUNING=1).
@@ -138,8 +144,10 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, StepUse use) {
     const int wide = dtype == DCP_F64 ? 2 : 4, most = sums ? kSumBlocks : kPlainBlocks;
     const int forced = env_int("DCP_TILE_SHAPE", -1);
     int shape = forced >= 0 && forced < num_shapes() ? forced : -1;
+    const bool adjoint = use == kAdjointStep, ragged = g.nx % wide != 0;
     // (vectors on ragged rows are compiled for the two shapes chosen here)
-    const bool one = !vec_ok || (dtype == DCP_F32 && g.nx <= 48) || (g.nx % wide != 0 && shape > 1);
+    const bool one = !vec_ok || (ragged && shape > 1) ||
+                     (dtype == DCP_F32 && (adjoint ? ragged && g.nx <= 64 : g.nx <= 48));
     const int vec = one ? 1 : wide;
     auto blocks = [&](int sh, int z) {
         const int nb = make_tile(g, vec, sh, z).nblk;
@@ -161,22 +169,34 @@ Tile pick_tile(int dtype, const Geo &g, bool vec_ok, StepUse use) {
             const int z = at_least(1, 8, 2, dtype == DCP_F64 ? 1200 : 900);
             pick(1, z == 2 && blocks(1, 2) < 512 ? 1 : z);
         };
-        if (one) pick(sums ? 0 : 1, sums ? at_least(0, 8, 1, 700) : at_least(1, 4, 1, 700));
-        else if (use == kRecomputeStep && blocks(1, 8) > most) pick(0, 8);
-        else if (use == kRecomputeStep || n8 < 410) few();
-        else if (n8 <= 512 && sums) pick(0, 8);
-        else if (n8 <= 512 && g.nx > 48 * vec) pick(1, 2);
-        else if (n8 <= 512) few();
-        else if (g.nx <= 48 * vec) {
+        const bool narrow = g.nx <= 48 * vec;
+        if (one) {
+            if (sums) pick(0, at_least(0, adjoint ? 4 : 8, 1, 700));
+            else pick(1, at_least(1, 4, 1, 700));
+        } else if (adjoint && blocks(1, 8) > most) {
+            pick(0, 8);
+        } else if (adjoint || n8 < 410) {
+            few();
+        } else if (n8 <= 512) {
+            if (sums) pick(0, 8);
+            else if (narrow) few();
+            else pick(1, 2);
+        } else if (narrow) {
             const int z = sums && g.nx <= 32 * vec && blocks(1, 16) >= 2048 ? 16 : 8;
             if (dtype == DCP_F64 && blocks(1, z) > most) pick(0, at_least(0, 64, 8, 2048));
             else pick(1, z);
+        } else if (n8 < 896) {
+            few();
+        } else if (n8 < 1024) {
+            if (sums) pick(0, 8);
+            else pick(1, 4);
+        } else if (n8 < 1152) {
+            pick(1, 8);
+        } else if (10 * g.nx < 6 * span) {
+            pick(0, at_least(0, 64, 8, 2048));
+        } else {
+            pick(0, sums ? 8 : 4);
         }
-        else if (n8 < 896) few();
-        else if (n8 < 1024) pick(sums ? 0 : 1, sums ? 8 : 4);
-        else if (n8 < 1152) pick(1, 8);
-        else if (10 * g.nx < 6 * span) pick(0, at_least(0, 64, 8, 2048));
-        else pick(0, sums ? 8 : 4);
         while (zc < 64 && blocks(shape, zc) > most) zc *= 2;
         if (forced != shape && blocks(shape, zc) > most) shape = 0;
     }
@@ -192,7 +212,7 @@ int max_blocks(int dtype, const Geo &g, StepUse use) {
     if (g.n == 0) return 0;
     const Tile a = pick_tile(dtype, g, true, use), b = pick_tile(dtype, g, false, use);
     if (a.nblk < 0 || b.nblk < 0) return -1;
-    return a.nblk > b.nblk ? a.nblk : b.nblk;
+    return std::max(a.nblk, b.nblk);
 }
 
 // ---------------------------------------------------------- workspace layout
@@ -331,7 +351,7 @@ int layout_adj(int dtype, const Geo &g, int32_t T, int32_t k, int32_t tblock, bo
         return DCP_OK;
     }
     if (g.n > 0) {
-        int nb = max_blocks(dtype, g, kSumStep);
+        int nb = max_blocks(dtype, g, kAdjointStep);
         if (nb < 0) return DCP_E_SHAPE;
         TbTile tb;
         if (tblock >= 2 && tb_plan(dtype, g.nx, g.ny, g.nz, true, kLdsMax, &tb) && tb.nblk > nb) nb = tb.nblk;
@@ -762,7 +782,7 @@ int layout_rev(int dtype, const Geo &g, int32_t T, int32_t nslots, bool lsum_fie
         return DCP_OK;
     }
     const size_t fb = align_up(g.bytes());
-    int nb = max_blocks(dtype, g, kRecomputeStep);
+    int nb = max_blocks(dtype, g, kAdjointStep);
     if (nb < 0) return DCP_E_SHAPE;
     BlkTile bk;
     if (blk_for(dtype, g, 2, kLdsMax, &bk) && bk.nblk > nb) nb = bk.nblk;
@@ -1137,7 +1157,8 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
     auto seg = [&](int32_t j) { return static_cast<void *>(at(ws, w.seg + (size_t)j * align_up(fb))); };
     auto slot = [&](int32_t c) { return static_cast<const void *>(static_cast<const char *>(ckpt) + (size_t)c * fb); };
     const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, lam[0], lam[1], lsum, ckpt, seg(0)});
-    const Tile t = pick_tile(dtype, g, vok, kSumStep);
+    const Tile t = pick_tile(dtype, g, vok, kAdjointStep);
+    const Tile tf = pick_tile(dtype, g, vok, kPlainStep);  // recomputation
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
     double *sums = reinterpret_cast<double *>(at(ws, w.sums));
     const int stride = w.nblk;
@@ -1185,7 +1206,7 @@ int dcp_adjoint_run(int dtype, const void *ckpt, int32_t ckpt_every, const void 
         for (int32_t j = 1; j < t1 - t0;) {
             const int32_t left = t1 - t0 - j;
             const int len = fpp.len_at(0, left);
-            DCP_TRY(fwd_pass(dtype, bc, g, c, t, fpp, len, prev, f, seg(j + len - 2),
+            DCP_TRY(fwd_pass(dtype, bc, g, c, tf, fpp, len, prev, f, seg(j + len - 2),
                              len >= 2 ? seg(j - 1) : nullptr, len == 3 ? seg(j) : nullptr, st));
             prev = seg(j + len - 2);
             j += len;
@@ -1282,7 +1303,7 @@ int dcp_revolve_forward(int dtype, void *u, const void *f, int64_t nx, int64_t n
     const RevBufs B{ws, &w, nslots, align_up(fb)};
     void *scratch = at(ws, w.scratch);
     const bool vok = vec_ok_for(dtype, g, {u, f, ws});
-    const Tile t = pick_tile(dtype, g, vok, kRecomputeStep);
+    const Tile tf = pick_tile(dtype, g, vok, kPlainStep);
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     DCP_TRY(launch_ew(dtype, EW_COPY, u, nullptr, B.buf(kRvOrigin), 0.0, g.n, ew_ok({u, B.buf(kRvOrigin)}), st));
@@ -1291,12 +1312,12 @@ int dcp_revolve_forward(int dtype, void *u, const void *f, int64_t nx, int64_t n
     int32_t last = kRvOrigin;
     for (const RvOp &op : ops) {
         if (op.kind != kRvAdvance) break;
-        if ((rc = rev_advance(dtype, bc, g, c, t, pp, f, B.buf(op.src), B.buf(op.dst), scratch, op.t1 - op.t0,
+        if ((rc = rev_advance(dtype, bc, g, c, tf, pp, f, B.buf(op.src), B.buf(op.dst), scratch, op.t1 - op.t0,
                               st)))
             return rc;
         last = op.dst;
     }
-    DCP_TRY(fused_step(dtype, bc, g, c, t, B.buf(last), f, u, nullptr, st));  // u_T
+    DCP_TRY(fused_step(dtype, bc, g, c, tf, B.buf(last), f, u, nullptr, st));  // u_T
     return DCP_OK;
 }
 
@@ -1347,7 +1368,8 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
     void *lam[2] = {at(ws, w.lam), at(ws, w.lam + align_up(fb))};
     void *lsum = grad_f ? grad_f : (lsum_field ? static_cast<void *>(at(ws, w.lsum)) : nullptr);
     const bool vok = vec_ok_for(dtype, g, {f, lam_T, grad_u0, grad_f, ws});
-    const Tile t = pick_tile(dtype, g, vok, kRecomputeStep);
+    const Tile t = pick_tile(dtype, g, vok, kAdjointStep);
+    const Tile tf = pick_tile(dtype, g, vok, kPlainStep);  // recomputation
     const PassPlan pp = plan_passes(dtype, DCP_FUSED, g, T, tblock, vok, false, 0);
     const dcp_coeffs &c = *coeffs;
     double *partials = reinterpret_cast<double *>(at(ws, w.partials));
@@ -1419,7 +1441,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
         if (op.kind == kRvAdvance && op.t1 - op.t0 == 1) {
             const int len = chain(i);
             if (len >= 2) {
-                DCP_TRY(fwd_pass(dtype, bc, g, c, t, pp, len, B.buf(op.src), f, B.buf(ops[i + len - 1].dst),
+                DCP_TRY(fwd_pass(dtype, bc, g, c, tf, pp, len, B.buf(op.src), f, B.buf(ops[i + len - 1].dst),
                                  B.buf(op.dst), len == 3 ? B.buf(ops[i + 1].dst) : nullptr, st));
                 i += len - 1;
                 continue;
@@ -1427,7 +1449,7 @@ int dcp_revolve_adjoint(int dtype, const void *f, const void *lam_T, int64_t nx,
         }
         const bool folded = fold(i);
         if (op.kind == kRvAdvance && !folded) {
-            if ((rc = rev_advance(dtype, bc, g, c, t, pp, f, B.buf(op.src), B.buf(op.dst), scratch,
+            if ((rc = rev_advance(dtype, bc, g, c, tf, pp, f, B.buf(op.src), B.buf(op.dst), scratch,
                                   op.t1 - op.t0, st)))
                 return rc;
             continue;
