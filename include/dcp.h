@@ -254,9 +254,11 @@ int dcp_run_plan(int dtype, int impl, int64_t nx, int64_t ny, int64_t nz,
  * symmetric under both boundary rules, so L^T is the same 7-point gather)
  * and accumulates the two parameter sums in double.
  * With tblock >= 2, two adjoint steps share one pass over memory where the
- * grid allows whole-row tiles, over blocks on small ones of these (adjoint steps are paired by global parity,
- * (2m+1, 2m), independently of k), and the recomputed forward steps take
- * passes of up to tblock steps, every state stored (as dcp_run plans them).
+ * grid allows whole-row tiles (over blocks on small ones of these, and on rows
+ * that are not whole 16-byte vectors only where a pair is the faster); adjoint
+ * steps are paired by global parity, (2m+1, 2m), independently of k, and the
+ * recomputed forward steps take passes of up to tblock steps, every state
+ * stored (as dcp_run plans them).
  *   ckpt        [ceil(T/k) fields] in: as written by dcp_run (same T, k,
  *               coefficients, boundary and dtype)
  *   f      [N]  in
