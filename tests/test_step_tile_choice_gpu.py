@@ -37,6 +37,7 @@ def _us(fn):
     ((100, 555, 810), F32, False),  # two fifths
     ((128, 720, 542), F32, True),   # half
     ((384, 706, 100), F32, True),   # several rounds
+    ((640, 500, 300), F64, True),   # runs of 7 planes
     ((512, 512, 64), F32, True),    # one full round
     ((192, 192, 192), F64, True),   # a little over one
     ((96, 96, 96), F64, True),      # far under one
