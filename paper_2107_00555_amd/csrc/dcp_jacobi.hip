@@ -656,16 +656,22 @@ int j2_pick_rpl(int64_t n0, int64_t n1, int64_t hh) {
 }
 
 // The row-marching form (j2m_kernel): used for arrays that give it at least
-// 2048 waves (two per SIMD) with row segments of at least 4*NH rows; passes of
+// 1900 waves (nearly two per SIMD) with row segments of at least 4*NH rows; passes of
 // 4 to 16 half-steps (even) that start with B (whole time-loop iterations).  More, shorter
 // segments even out the end of a pass (a share of about 2048 / waves of it)
 // but recompute 2*NH rows each; their sum is least near
 // sqrt(768 * n0 * strips / NH) waves.  Measured with 16 half-steps, us per
 // half-step with 4096 / 8192 / 16384 / 24576 waves: 46800^2 906 / 807 / 736 /
 // 720 (the rule gives 33,000), 23400^2 221 / 194 / 183 / 186 (16,500),
-// 12000^2 54 / 52 / 55 / 58 (8,500).  Below the 2048 waves the region tiles
-// are as fast: 3000^2 5.4-6.1 against 5.6 us.  DCP_J2_MODE = 3 forces the form
-// where it applies, 1 or 2 the region tiles (tuning runs only).
+// 12000^2 54 / 52 / 55 / 58 (8,500).  Below the 1900 waves the region tiles
+// are as fast: 3000^2 5.4-6.1 against 5.6 us (3500^2, 1998 waves, 7.9 against 5.8).
+// Passes of up to 10 half-steps march from 2^24 elements on, where the array read and
+// the one written no longer fit the 256 MB cache, from which the tiles' halos come.
+// 200 half-steps, ms, tiles / march, in passes of 4: 3000^2 1.55 / 2.16, 4000^2 2.58 /
+// 3.46, 4500^2 4.06 / 4.02, 5500^2 6.33 / 5.87; of 8: 1.02 / 1.12, 1.71 / 1.79, 2.32 /
+// 2.24, 3.55 / 3.48; of 12: 1.02 / 1.04, 1.76 / 1.74, 2.26 / 1.95, 3.44 / 2.82.
+// DCP_J2_MODE = 3 forces the form where it applies, 1 or 2 the region tiles (tuning
+// runs only).
 struct J2MPlan {
     bool use = false;
     int strips = 0, segs = 0, seg_rows = 0;
@@ -684,7 +690,7 @@ J2MPlan j2m_pick(int64_t n0, int64_t n1, int64_t hh) {
     m.seg_rows = (int)((n0 + segs - 1) / segs);
     m.segs = (int)((n0 + m.seg_rows - 1) / m.seg_rows);
     m.strips = (int)strips;
-    m.use = (int64_t)m.strips * m.segs >= 2048;
+    m.use = (int64_t)m.strips * m.segs >= 1900 && (hh > 10 || n0 * n1 >= ((int64_t)1 << 24));
     const char *fm = dcp::tuning_env("DCP_J2_MODE");
     if (fm && *fm) m.use = std::atoi(fm) == 3;
     return m;
