@@ -661,20 +661,21 @@ struct PairPlan {
 // Whether pairs over whole rows pay on rows that are not whole vectors.  A plane of a
 // tile's run takes as long on short rows, which leave most of its 1024 lanes idle, where
 // single steps take less.  The rule prices a pair by its planes in sequence and the
-// chunks of a row, two single steps by the grid's rows and their points, us, each with a
-// launch; fitted to 310 gradients on 155 such grids, with the running sum and without.
-// Four steps, us, single and in pairs: FP32 31 x 700 x 1612 1090 / 2510, 161 x 700 x 310
-// 369 / 595, 255 x 400 x 98 116 / 100; FP64 31 x 700 x 1612 1370 / 2220, 255 x 400 x 98
-// 223 / 135.  Against single elements the choice gains 1.94x in the mean and 0.95x at the
-// least, always pairs 1.81x and 0.45x, never 1.57x and 0.95x.  With the running sum pairs
-// pay a little sooner (FP32 1001 x 300 x 100, four steps: 834 us, single 1094): one choice
-// for both keeps the parameter sums the same.  Rows of whole vectors take pairs throughout.
+// chunks of a plane's frame, two single steps by the grid's rows and their points, us,
+// each with a launch; fitted to 478 gradients on 239 such grids, with the running sum and
+// without.  Four steps, us, single and in pairs: FP32 31 x 700 x 1612 1090 / 2510, 161 x
+// 700 x 310 369 / 595, 255 x 400 x 98 116 / 100, 818 x 157 x 103 with the sum 317 / 171;
+// FP64 31 x 700 x 1612 1370 / 2220, 255 x 400 x 98 223 / 135.  Against single elements
+// the choice gains 2.21x in the mean and 0.95x at the least, always pairs 2.12x and
+// 0.45x, never 1.69x and 0.95x.  With the running sum pairs pay a little sooner (FP32 74 x
+// 147 x 266, four steps: 123 us, single 155): one choice for both keeps the parameter
+// sums the same.  Rows of whole vectors take pairs throughout.
 bool pair_pays(int dtype, const Geo &g, const TbTile &tb) {
     const bool f64 = dtype == DCP_F64;
-    const double chunks = (double)((g.nx + (f64 ? 1 : 3)) / (f64 ? 2 : 4)), launch = f64 ? 4.2 : 3.1;
+    const double frame = (double)(tb.ty + 4) * (double)((g.nx + tb.vec - 1) / tb.vec), launch = f64 ? 6.5 : 7.8;
     const double planes = (double)((tb.nblk + 255) / 256) * (double)(tb.zc + 4), rows = 1e-3 * (double)(g.ny * g.nz);
-    const double pair = launch + planes * (f64 ? 1.89 + 0.0073 * chunks : 0.98 + 0.0104 * chunks);
-    const double step = launch + rows * (f64 ? 0.476 + 0.0043 * (double)g.nx : 0.177 + 0.0018 * (double)g.nx);
+    const double pair = launch + planes * (f64 ? 1.61 + 0.000375 * frame : 0.73 + 0.000717 * frame);
+    const double step = launch + rows * (f64 ? 0.328 + 0.0046 * (double)g.nx : 0.067 + 0.0016 * (double)g.nx);
     return pair <= 2.0 * step;
 }
 

@@ -78,6 +78,8 @@ def test_single_steps_take_a_fast_tile(monkeypatch, shape, dtype, full):
     ((31, 700, 1612), F64, False),
     ((255, 400, 98), F64, True),
     ((451, 300, 100), F32, True),
+    ((977, 148, 62), F32, True),   # frames of eight rows
+    ((429, 423, 38), F64, True),
 ])
 def test_pairs_on_ragged_rows_where_they_pay(shape, dtype, pays):
     say("adjoint pairs", shape, dtype)
