@@ -914,7 +914,9 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
     // one-dimensional grid of at most 2^20 workgroups strides over them.  zr
     // doubles, up to 16, while at least 4096 workgroups (16 per CU) remain, 2048
     // of twice the rows (with 4096 of these, whose runs were half as long, steps of
-    // 160 x 528 x 47 FP64 took 35.7 us, 30.6 so; 1.05 times as long over 200 steps).
+    // 160 x 528 x 47 FP64 took 35.7 us, 30.6 so; 1.05 times as long over 200 steps) but
+    // for runs of 16 (FP32 640 x 480 x 200 in runs of 8 128.0, with 2340 workgroups in
+    // runs of 16 134.4; 32 x 386 x 922 88.9 / 95.7).
     const int64_t tile_w = p->dtype == DCP_F64 ? 128 : 256;
     int64_t tiles_x = (nx + tile_w - 1) / tile_w;
     double smax[3] = {0, 0, 0};  // largest |offset| of any shifted read, per axis
@@ -939,7 +941,8 @@ int dcp_fuse_run(dcp_fused *p, const void *const *inputs, const double *params, 
         const int wg_rows = two ? 2 * kRows : kRows;
         const int64_t yblocks = (ny + wg_rows - 1) / wg_rows;
         int64_t zr = 1;
-        while (zr < 16 && tiles_x * yblocks * ((nz + 2 * zr - 1) / (2 * zr)) >= 4096 * kRows / wg_rows) zr *= 2;
+        auto least = [&](int64_t z) { return z < 16 ? 4096 * kRows / wg_rows : 4096; };
+        while (zr < 16 && tiles_x * yblocks * ((nz + 2 * zr - 1) / (2 * zr)) >= least(2 * zr)) zr *= 2;
         if (const char *e = dcp::tuning_env("DCP_FUSE_ZR")) {  // tuning override: planes per wave tile
             const long v = std::strtol(e, nullptr, 10);
             if (v >= 1 && v <= 4096) zr = v;

@@ -44,3 +44,26 @@ def test_runs_of_two_rows_are_among_the_fastest(monkeypatch, shape):
         others[zr] = _us(lambda: prog.run(ins, {}, bc=0))
     print(f"took {took:.1f}", {k: round(v, 1) for k, v in others.items()})
     assert took <= 1.14 * min(others.values())
+
+
+# runs repeat within 1%, and the rule picks the fastest run on these grids
+@pytest.mark.parametrize("shape", [(640, 480, 200), (32, 386, 922), (677, 137, 721)])
+def test_long_runs_leave_enough_workgroups(monkeypatch, shape):
+    from paper_2107_00555_amd import fuse
+    nx, ny, nz = shape
+    P = fuse.Program("f32")
+    u, f = P.input("u", "f")
+    P.output("v", u + 0.1 * (fuse.lap7(u, 1.0) - 0.1 * ((u * u) * u) + 0.5 * f))
+    prog = P.compile()
+    g = torch.Generator(device=DEV).manual_seed(nx)
+    ins = [torch.rand((nz, ny, nx), dtype=torch.float32, device=DEV, generator=g) for _ in range(2)]
+    say("generated long runs", shape)
+    _us(lambda: prog.run(ins, {}, bc=0))
+    took = _us(lambda: prog.run(ins, {}, bc=0))
+    monkeypatch.setenv("DCP_TUNING", "1")
+    others = {}
+    for zr in (8, 16):
+        monkeypatch.setenv("DCP_FUSE_ZR", str(zr))
+        others[zr] = _us(lambda: prog.run(ins, {}, bc=0))
+    print(f"took {took:.1f}", {k: round(v, 1) for k, v in others.items()})
+    assert took <= 1.03 * min(others.values())
