@@ -277,24 +277,21 @@ __global__ void __launch_bounds__(1024, RPL <= 4 ? 8 : 4) j2_kernel(J2Args a) {
         double va[RPL][VEC], vb[RPL][VEC];
         load(a.ain, va);
         // B: its own values when the pass starts with A, else only the boundary
-        // cells count (its interior is written before it is read).  A tile that
-        // holds some reads its rows' end cells in every lane, without a guard: on a
-        // narrow array most tiles do, and reading their whole rows cost them
-        // another array's traffic (20000 x 600, 2 half-steps per pass: 1136 us, 1019
-        // with a guard for each cell).
+        // cells count (its interior is written before it is read).  A wave without
+        // a boundary row reads one cell a row, the end its lane may hold: on a narrow
+        // array most tiles hold some, and reading their whole rows cost them another
+        // array's traffic (20000 x 600, 2 half-steps per pass: 1133 us, 929 so).  Two
+        // cells a row in every wave cost the others their loads' latency (601 steps of
+        // 682 x 6005 3.79 ms, 3.69 so; 300 of 1300^2 916 us, 903).
         if (a.phase) {
             load(a.bin, vb);
         } else if constexpr (decltype(masked)::value) {
+            if (gr <= 0 || gr + RPL >= n0) {
+                load(a.bfix, vb);
+            } else {  // (a lane holds one end at most: three columns or more)
+                const double *rb = a.bfix + gr * n1 + (gc <= 0 ? 0 : n1 - 1);
 #pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int64_t i = gr + r;
-                const bool whole = i <= 0 || i >= n0 - 1;  // a boundary row
-                const double *rb = a.bfix + min(max(i, (int64_t)0), n0 - 1) * n1;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const int j = gc + v, end = j <= 0 ? 0 : n1 - 1;
-                    vb[r][v] = rb[whole ? min(max(j, 0), n1 - 1) : end];
-                }
+                for (int r = 0; r < RPL; ++r) vb[r][0] = vb[r][1] = rb[(int64_t)r * n1];
             }
         } else {
 #pragma unroll
